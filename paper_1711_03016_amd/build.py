@@ -17,7 +17,7 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 INCLUDE = os.path.join(ROOT, "include")
 LIB = os.path.join(HERE, "libdlvm.so")
-SOURCES = ["gemm.hip", "gemm_nn.hip", "gemm_nt.hip", "gemm_tn.hip", "gemm_pair.hip",
+SOURCES = ["gemm.hip", "gemm_nn.hip", "gemm_nt.hip", "gemm_tn.hip", "gemm_pair.hip", "gemm_wave.hip", "gemm_f32.hip",
            "elementwise.hip", "small_step.hip", "api.cpp"]
 
 HIPCC = shutil.which("hipcc") or "/opt/rocm/bin/hipcc"

@@ -628,7 +628,7 @@ dlvm_status plan_gradient(const dlvm_model* m, const void* params, const void* x
       // workspace, xbar into dx, one loss partial per wavefront.
       GemmDesc d = gemm_nn(dt, DLVM_F32, DLVM_ACT_NONE, batch, N, K, 1.0f, x, P(0), N, P(1), zbar, N);
       d.aux = x;
-      d.chain_epilogue = true;
+      d.chain_epilogue = d.chain_product = true;
       d.C2 = dx;
       d.partials = partials;
       d.inv_n = scale;
@@ -641,9 +641,9 @@ dlvm_status plan_gradient(const dlvm_model* m, const void* params, const void* x
       st = run.run(std::move(info), [&](hipStream_t s) { return dlvm::launch_gemm(d, pl, s); },
                    "chain product launch");
     } else {
-      if ((st = run.gemm(gemm_nn(dt, DLVM_F32, DLVM_ACT_NONE, batch, N, K, 1.0f, x, P(0), N,
-                                 nullptr, z, N))) != DLVM_OK)
-        return st;
+      GemmDesc zd = gemm_nn(dt, DLVM_F32, DLVM_ACT_NONE, batch, N, K, 1.0f, x, P(0), N, nullptr, z, N);
+      zd.chain_product = true;
+      if ((st = run.gemm(zd)) != DLVM_OK) return st;
       np = dlvm::chain8_partials(batch, N);
       st = run.run(elementwise_info("chain8", batch, N, 16.0 * double(batch) * N + 4.0 * N),
                    [&](hipStream_t s) {

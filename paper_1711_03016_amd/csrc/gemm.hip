@@ -17,27 +17,28 @@ constexpr double kRateBF16 = 4096.0;
 constexpr double kL2BytesPerClock = 64.0;
 
 // Tile configurations with the fraction of the matrix-core rate each sustains
-// when not starved, for float32 and for bf16 operands (measured on large
-// products). Configurations 0-5 are the register-staged kernel
-// (gemm_kernel.hpp), 10-13, 16 and 17 the bf16 kernel with direct-to-LDS loads
-// (gemm_async.hpp; 18 with two k-groups of waves), 14-15 the four-wave bf16
-// kernel (gemm_xl.hpp).
+// with bf16 operands when not starved (measured on large products).
+// Configurations 0-5 are the register-staged kernel (gemm_kernel.hpp), 10-13, 16
+// and 17 the bf16 kernel with direct-to-LDS loads (gemm_async.hpp; 18 and 19 with
+// two k-groups of waves), 14-15 the four-wave bf16 kernel (gemm_xl.hpp). Float32
+// products run on 6-9 (gemm_wave.hpp) and 20-22 (gemm_f32.hpp); 3 is left to them
+// for leading dimensions whose byte offsets those cannot hold.
 struct TileShape {
   int cfg;
   int bm, bn;
-  double eff_f32, eff_bf16;
+  double eff_bf16;
   bool async;
   int kseg;  // register-staged kernel: 128-byte k-segments per pipeline stage
 };
 constexpr TileShape kTiles[] = {
-    {0, 128, 128, 0.8, 0.55, false, 1},  {1, 64, 64, 0.6, 0.3, false, 2},
-    {2, 128, 32, 0.6, 0.3, false, 2},    {3, 32, 32, 0.5, 0.25, false, 4},
-    {4, 64, 64, 0.65, 0.2, false, 2},    {5, 32, 32, 0.5, 0.25, false, 8},
-    {10, 256, 256, 0.0, 0.9, true, 0},   {11, 256, 128, 0.0, 0.63, true, 0},
-    {12, 128, 128, 0.0, 0.54, true, 0},  {13, 256, 256, 0.0, 0.88, true, 0},
-    {14, 256, 256, 0.0, 0.89, true, 0},  {15, 256, 256, 0.0, 0.85, true, 0},
-    {16, 64, 128, 0.0, 0.5, true, 0},    {17, 128, 128, 0.0, 0.54, true, 0},
-    {18, 64, 128, 0.0, 0.55, true, 0},   {19, 128, 128, 0.0, 0.56, true, 0}};
+    {0, 128, 128, 0.55, false, 1}, {1, 64, 64, 0.3, false, 2},    {2, 128, 32, 0.3, false, 2},
+    {3, 32, 32, 0.25, false, 4},   {4, 64, 64, 0.2, false, 2},    {5, 32, 32, 0.25, false, 8},
+    {10, 256, 256, 0.9, true, 0},  {11, 256, 128, 0.63, true, 0}, {12, 128, 128, 0.54, true, 0},
+    {13, 256, 256, 0.88, true, 0}, {14, 256, 256, 0.89, true, 0}, {15, 256, 256, 0.85, true, 0},
+    {16, 64, 128, 0.5, true, 0},   {17, 128, 128, 0.54, true, 0}, {18, 64, 128, 0.55, true, 0},
+    {19, 128, 128, 0.56, true, 0}, {20, 128, 128, 0.0, false, 0}, {22, 128, 64, 0.0, false, 0},
+    {21, 64, 64, 0.0, false, 0},   {9, 64, 64, 0.0, false, 0},    {8, 32, 32, 0.0, false, 0},
+    {7, 16, 32, 0.0, false, 0},    {6, 16, 16, 0.0, false, 0}};
 
 // The register-staged kernel has one stage of loads in flight: a stage costs
 // at least one load round trip (measured on small float32 products).
@@ -110,9 +111,54 @@ bool xl_phases_ok(const GemmDesc& d) {
          d.N <= d.ldb;
 }
 
+// The float32 kernel that loads its fragments from global memory (configurations
+// 6-9): any size and alignment; the byte offsets inside a step (up to 64 rows)
+// stay below 2^31.
+bool wave_config(int cfg) { return cfg >= 6 && cfg <= 9; }
+bool wave_ok(const GemmDesc& d) {
+  const int64_t lim = int64_t(1) << 22;
+  return d.dtype == F32 && !d.chain_product && d.lda <= lim && d.ldb <= lim &&
+         (!two_phase(d) || d.lda2 <= lim);
+}
+
+// The float32 kernel with direct-to-LDS loads (configurations 20-22): any size
+// and alignment; the byte offsets inside a k-tile stay below 2^31.
+bool f32_config(int cfg) { return cfg >= 20 && cfg <= 22; }
+bool f32_ok(const GemmDesc& d) {
+  const int64_t lim = int64_t(1) << 20;
+  return d.dtype == F32 && d.lda <= lim && d.ldb <= lim && (!two_phase(d) || d.lda2 <= lim);
+}
+
 // k per slice when K is split `splits` ways (a multiple of 64, so every
 // slice but the last is whole k-tiles for every kernel).
 int64_t slice_k(int64_t K, int splits) { return ceil_div(ceil_div(K, splits), 64) * 64; }
+
+// Clock cycles a float32 product needs on configuration t with tiles of kc k,
+// `slots` tile-slices in all: rounds of tiles over the compute units, each its
+// matrix-core cycles (256 flops a cycle) times what the kernel takes over them,
+// plus launch, first loads and epilogue. Fitted to back-to-back launches of
+// 8 x 64 x 64 to 8192 x 4096 x 4096 (2,400 cycles a us). Waves that share the
+// contraction (6-9): the smaller the tile, the more the operand loads weigh,
+// most where both operands are k-contiguous (NT: each 16-byte load of a wave
+// touches 16 rows). Tiles in LDS (20-22): at 1.1-1.2 times the matrix cycles once
+// several tiles share a compute unit, far from it with one.
+double estimate_f32(const GemmDesc& d, const TileShape& t, int64_t slots, int64_t kc) {
+  const double rounds = double(ceil_div(slots, kComputeUnits));
+  const double mfma = 2.0 * t.bm * t.bn * double(kc) / kRateF32;
+  const int lay = static_cast<int>(d.layout);
+  double over, fixed = 6000.0;
+  switch (t.cfg) {
+    case 6: { const double o[] = {2.7, 4.0, 2.5}; over = o[lay]; break; }
+    case 7: { const double o[] = {2.3, 3.1, 1.9}; over = o[lay]; break; }
+    case 8: { const double o[] = {1.9, 2.7, 1.7}; over = o[lay]; break; }
+    case 9: { const double o[] = {1.6, 1.65, 1.4}; over = o[lay]; break; }
+    case 20: over = 1.08 + 0.4 / rounds; fixed = 8000.0; break;
+    case 22: over = 1.13 + 0.55 / rounds; fixed = 8000.0; break;
+    case 21: over = 1.16 + 0.8 / rounds; fixed = 8000.0; break;
+    default: over = 4.0; break;  // 3: unaligned element loads through registers
+  }
+  return fixed + rounds * mfma * over;
+}
 
 // Clock cycles one configuration needs: rounds of tiles over the compute
 // units, each tile bound by its matrix-core work or its operand traffic, plus
@@ -121,18 +167,21 @@ double estimate(const GemmDesc& d, const TileShape& t, int splits) {
   const int64_t tiles = ceil_div(d.M, t.bm) * ceil_div(d.N, t.bn);
   const int64_t kc = splits > 1 ? slice_k(d.K, splits) : d.K;
   const int64_t slices = ceil_div(d.K, kc);
-  const double es = d.dtype == F32 ? 4.0 : 2.0;
-  const double eff = d.dtype == F32 ? t.eff_f32 : t.eff_bf16;
-  const double rate = (d.dtype == F32 ? kRateF32 : kRateBF16) * eff;
-  const double flops = 2.0 * t.bm * t.bn * double(kc);
-  const double bytes = double(t.bm + t.bn) * double(kc) * es;
-  double per_tile = std::max(flops / rate, bytes / kL2BytesPerClock);
-  if (!t.async && d.dtype == BF16) {  // (the float32 choices were measured without it)
-    const int64_t kstage = int64_t(t.kseg) * 64;
-    per_tile = std::max(per_tile, double(ceil_div(kc, kstage)) * kStageCycles);
+  double c;
+  if (d.dtype == F32) {
+    c = estimate_f32(d, t, tiles * slices, kc);
+  } else {
+    const double rate = kRateBF16 * t.eff_bf16;
+    const double flops = 2.0 * t.bm * t.bn * double(kc);
+    const double bytes = double(t.bm + t.bn) * double(kc) * 2.0;
+    double per_tile = std::max(flops / rate, bytes / kL2BytesPerClock);
+    if (!t.async) {
+      const int64_t kstage = int64_t(t.kseg) * 64;
+      per_tile = std::max(per_tile, double(ceil_div(kc, kstage)) * kStageCycles);
+    }
+    per_tile += kTileFixed;
+    c = double(ceil_div(tiles * slices, kComputeUnits)) * per_tile;
   }
-  per_tile += kTileFixed;
-  double c = double(ceil_div(tiles * slices, kComputeUnits)) * per_tile;
   if (slices > 1) c += kLaunch + double(slices + 1) * double(d.M) * double(d.N) * 4.0 / kHbmBytesPerClock;
   return c;
 }
@@ -202,6 +251,9 @@ GemmPlan choose(const GemmDesc& d, bool assume_aligned, int64_t capacity, int fo
   for (const TileShape& t : kTiles) {
     if (t.cfg == 2 && d.N > 32) continue;  // the narrow tile only for narrow outputs
     if (t.cfg == 5 && forced != 5) continue;
+    if (wave_config(t.cfg) && !wave_ok(d)) continue;
+    if (f32_config(t.cfg) && !f32_ok(d)) continue;
+    if (d.dtype == F32 && !wave_config(t.cfg) && !f32_config(t.cfg) && (t.cfg != 3 || f32_ok(d))) continue;
     if (t.async && !can_async) continue;
     if (t.async && d.dtype == F32) continue;
     // Measured: where the direct-to-LDS kernels can run a bf16 product, the
@@ -278,7 +330,7 @@ GemmPlan choose(const GemmDesc& d, bool assume_aligned, int64_t capacity, int fo
   }
   if (best == nullptr) {  // a forced configuration or split that cannot run is ignored
     if (forced >= 0 || fsplits > 0) return choose(d, assume_aligned, capacity, -1, -1);
-    best = &kTiles[3];      // (not reached: the 32 x 32 tile runs every product unsplit)
+    best = &kTiles[3];      // (not reached: some tile runs every product unsplit)
     best_s = 1;
   }
   GemmPlan pl{};
@@ -295,8 +347,7 @@ GemmPlan choose(const GemmDesc& d, bool assume_aligned, int64_t capacity, int fo
 }  // namespace
 
 int64_t chain_partials(const GemmPlan& pl) {
-  // wavefronts of a tile (waves along M x N) of the register-staged configurations
-  const int waves = (pl.cfg == 3 || pl.cfg == 5) ? 1 : 4;
+  const int waves = 4;  // (configurations 20-22: 2 x 2)
   return static_cast<int64_t>(pl.tiles_m) * pl.tiles_n * waves;
 }
 
@@ -346,6 +397,15 @@ void vector_ok(const GemmDesc& d, bool& va, bool& vb) {
     va = va && phases_ok(d, vw);
     if (d.layout != Layout::NN) vb = vb && d.K1 % vw == 0;
   }
+}
+
+// Whether every operand row of a float32 product starts on 16 bytes and every
+// 16-byte load of the direct-to-LDS kernel lies inside or outside the operand.
+bool vec16(const GemmDesc& d) {
+  bool va, vb;
+  vector_ok(d, va, vb);
+  if (two_phase(d) && d.K1 % 4 != 0) return false;
+  return va && vb;
 }
 
 // Whether a launch loads its operands through buffer descriptors (and needs
@@ -422,6 +482,8 @@ hipError_t launch_gemm(const GemmDesc& d, const GemmPlan& pl, hipStream_t s) {
     return hipErrorInvalidValue;
   const gemm::Params p = make_params(d, pl);
   const unsigned grid = grid_of(pl);
+  if (wave_config(pl.cfg)) return gemm::launch_wave(p, d.layout, pl.cfg, grid, s);
+  if (f32_config(pl.cfg)) return gemm::launch_f32(p, d.layout, pl.cfg, grid, vec16(d), s);
   const int out = pl.splits > 1 ? F32 : d.out_dtype;  // split slices: float32 partials
   switch (d.layout) {
     case Layout::NN: return gemm::launch_nn(p, d.dtype, out, pl.cfg, grid, va, vb, s);
@@ -433,9 +495,9 @@ hipError_t launch_gemm(const GemmDesc& d, const GemmPlan& pl, hipStream_t s) {
 
 bool pairable(const GemmDesc& tn, const GemmPlan& ptn, const GemmDesc& nt, const GemmPlan& pnt) {
   if (tn.layout != Layout::TN || nt.layout != Layout::NT || tn.dtype != nt.dtype) return false;
-  if (ptn.cfg != pnt.cfg || !gemm::pair_config(tn.dtype, ptn.cfg)) return false;
+  if (!gemm::pair_config(tn.dtype, ptn.cfg, pnt.cfg)) return false;
   if ((buffer_loads(tn, ptn) && !xl_ok(tn)) || (buffer_loads(nt, pnt) && !xl_ok(nt))) return false;
-  if (ptn.cfg < 10) {  // register-staged: 16-byte loads for all four operands
+  if (ptn.cfg < 6) {  // register-staged: 16-byte loads for all four operands
     bool a1, b1, a2, b2;
     vector_ok(tn, a1, b1);
     vector_ok(nt, a2, b2);
@@ -452,6 +514,9 @@ hipError_t launch_gemm_pair(const GemmDesc& tn, const GemmPlan& ptn, const GemmD
   if (nt.mask != nullptr && (!mask_ok(nt, pnt) || !aligned16(nt.mask))) return hipErrorInvalidValue;
   const gemm::Params p1 = make_params(tn, ptn), p2 = make_params(nt, pnt);
   const unsigned n1 = grid_of(ptn);
+  if (tn.dtype == F32)
+    return gemm::launch_f32_pair(p1, p2, static_cast<int>(n1), n1 + grid_of(pnt), ptn.cfg, pnt.cfg,
+                                 vec16(tn) && vec16(nt), s);
   return gemm::launch_pair(p1, p2, static_cast<int>(n1), n1 + grid_of(pnt), tn.dtype,
                            nt.out_dtype, ptn.cfg, s);
 }

@@ -714,9 +714,28 @@ hipError_t launch_vec(const Params& p, int cfg, unsigned grid, bool va, bool vb,
             : launch_cfg<T, TO, AK, BKM, false, false, EPI, PH2>(p, cfg, grid, s);
 }
 
+// Float32 products whose leading dimensions are beyond the byte offsets of the
+// other float32 kernels: configuration 3 with element loads.
+template <bool AK, bool BKM, int EPI, bool PH2 = false>
+hipError_t launch_f32_far(const Params& p, int cfg, unsigned grid, hipStream_t s) {
+  if (cfg != 3) return hipErrorInvalidValue;
+  launch_kernel((dlvm_gemm_kernel<float, float, AK, BKM, 32, 32, 1, 1, 4, 4, false, false, EPI, PH2>),
+                dim3(grid), dim3(256), s, p);
+  return hipGetLastError();
+}
+
+// Float32 products of the waves that share the contraction (gemm_wave.hpp,
+// configurations 6-9). One translation unit.
+hipError_t launch_wave(const Params& p, Layout layout, int cfg, unsigned grid, hipStream_t s);
+// Large float32 products staged in LDS by direct loads (gemm_f32.hpp,
+// configurations 20-22); vec: 16-byte loads.
+hipError_t launch_f32(const Params& p, Layout layout, int cfg, unsigned grid, bool vec, hipStream_t s);
+
 // The two adjoint products of a layer (TN wrt the weights, NT wrt the input)
-// in one launch, for the configurations pair_config accepts.
-bool pair_config(int dtype, int cfg);
+// in one launch, for the configurations (of the two) pair_config accepts.
+bool pair_config(int dtype, int cfg_tn, int cfg_nt);
+hipError_t launch_f32_pair(const Params& p1, const Params& p2, int n1, unsigned grid, int cfg_tn,
+                           int cfg_nt, bool vec, hipStream_t s);
 hipError_t launch_pair(const Params& p1, const Params& p2, int n1, unsigned grid, int dtype,
                        int out_dtype2, int cfg, hipStream_t s);
 

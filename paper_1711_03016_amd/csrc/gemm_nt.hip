@@ -7,7 +7,7 @@ namespace gemm {
 
 hipError_t launch_nt(const Params& p, int dtype, int out_dtype, int cfg, unsigned grid, bool va,
                      bool vb, hipStream_t s) {
-  if (dtype == F32) return launch_vec<float, float, true, true, EPI_DACT>(p, cfg, grid, va, vb, s);
+  if (dtype == F32) return launch_f32_far<true, true, EPI_DACT>(p, cfg, grid, s);
   if (cfg >= kAsyncFirst) {
     if (out_dtype == F32) return launch_bf16<float, true, true, EPI_DACT>(p, cfg, grid, s);
     return launch_bf16<bf16_t, true, true, EPI_DACT>(p, cfg, grid, s);

@@ -1,26 +1,26 @@
 // Instantiations of the paired launch of a layer's two adjoint products (TN
-// wrt the weights, NT wrt the input): register-staged configurations 0 and 3,
-// direct-to-LDS configurations 10 and 12.
+// wrt the weights, NT wrt the input) of bf16 networks: register-staged
+// configuration 3, direct-to-LDS configurations 10 and 12.
 #include "gemm_xl.hpp"
 
 namespace dlvm {
 namespace gemm {
 
-bool pair_config(int dtype, int cfg) {
-  if (dtype == F32) return cfg == 0 || cfg == 3;
-  return cfg == 3 || cfg == 10 || cfg == 12;
+bool pair_config(int dtype, int cfg_tn, int cfg_nt) {
+  if (dtype == F32) {
+    // (6, 7 and 8 have the same number of waves, so any two of them share a launch)
+    const bool w1 = cfg_tn >= 6 && cfg_tn <= 8, w2 = cfg_nt >= 6 && cfg_nt <= 8;
+    return (w1 && w2) || (cfg_tn == cfg_nt && (cfg_tn == 9 || (cfg_tn >= 20 && cfg_tn <= 22)));
+  }
+  return cfg_tn == cfg_nt && (cfg_tn == 3 || cfg_tn == 10 || cfg_tn == 12);
 }
 
 namespace {
 
 template <typename T, typename TO2>
-hipError_t launch_reg_pair(const Params& p1, const Params& p2, int n1, unsigned grid, int cfg,
+hipError_t launch_reg_pair(const Params& p1, const Params& p2, int n1, unsigned grid,
                            hipStream_t s) {
-  if (cfg == 0)
-    launch_kernel((dlvm_gemm_pair_kernel<T, TO2, 128, 128, 2, 2, 1, 1>), dim3(grid), dim3(256), s,
-                  p1, p2, n1);
-  else
-    launch_kernel((dlvm_gemm_pair_kernel<T, TO2, 32, 32, 1, 1, 4, 4>), dim3(grid), dim3(256), s,
+  launch_kernel((dlvm_gemm_pair_kernel<T, TO2, 32, 32, 1, 1, 4, 4>), dim3(grid), dim3(256), s,
                   p1, p2, n1);
   return hipGetLastError();
 }
@@ -41,13 +41,12 @@ hipError_t launch_async_pair(const Params& p1, const Params& p2, int n1, unsigne
 
 hipError_t launch_pair(const Params& p1, const Params& p2, int n1, unsigned grid, int dtype,
                        int out_dtype2, int cfg, hipStream_t s) {
-  if (dtype == F32) return launch_reg_pair<float, float>(p1, p2, n1, grid, cfg, s);
   if (cfg >= kAsyncFirst) {
     if (out_dtype2 == F32) return launch_async_pair<float>(p1, p2, n1, grid, cfg, s);
     return launch_async_pair<bf16_t>(p1, p2, n1, grid, cfg, s);
   }
-  if (out_dtype2 == F32) return launch_reg_pair<bf16_t, float>(p1, p2, n1, grid, cfg, s);
-  return launch_reg_pair<bf16_t, bf16_t>(p1, p2, n1, grid, cfg, s);
+  if (out_dtype2 == F32) return launch_reg_pair<bf16_t, float>(p1, p2, n1, grid, s);
+  return launch_reg_pair<bf16_t, bf16_t>(p1, p2, n1, grid, s);
 }
 
 }  // namespace gemm

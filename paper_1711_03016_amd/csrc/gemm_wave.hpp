@@ -1,0 +1,408 @@
+// Float32 dense-layer products whose waves load their matrix-core fragments
+// straight from global memory and share the contraction between them.
+//
+// Same products and fused epilogues as gemm_kernel.hpp (NN forward, NT adjoint
+// wrt the input, TN adjoint wrt the weights). A workgroup of NW waves owns one
+// tile of 16 AB x 16 BB outputs; every wave computes the whole tile over its own
+// contiguous range of k-steps (16 k each), and the NW partial tiles are added
+// in wave order through LDS at the end, where the epilogue runs.
+//
+// What bounds these products is not arithmetic: with a few hundred tiles each
+// compute unit has one, and its time is the latency of reaching the operands.
+// Staged through LDS, every k-stage cost a memory round trip and a barrier
+// (about 3,500 cycles per 128 k). Here the loads of DEPTH steps are in flight
+// per wave, no barrier stands between the first load and the one reduction,
+// and the operands cross no LDS. Measured back to back on 256 x 512 outputs
+// (rotating operands): K 784 12.5 -> 5.4 us, K 512 10 -> 4.1 us; 64 x 256 x 356
+// (a recurrent cell) 9.2 -> 2.8 us; 512 x 512 x 256 wrt the weights 8 -> 4.1 us.
+//
+// Fragments without a transpose. v_mfma_f32_16x16x4_f32 wants, in lane
+// 16 g + l, the value of row (or column) l at the g-th of its 4 k. Both
+// operands may use any assignment of k to (instruction, g) as long as they use
+// the same one, and rows may be assigned to lanes in any order that the store
+// undoes, so:
+//   k-contiguous operand: one 16-byte load per 16-row block, lane (g, l)
+//     taking k = 4 g .. 4 g + 3 of row l; value e feeds instruction e.
+//   row-contiguous operand (its k strided in memory): for each e one load of
+//     the 16 * R columns of row k = 4 g + e, lane l taking columns R l .. R l + R - 1
+//     (R = AB or BB, a 4 R byte load); value i belongs to block i, whose row l
+//     is thus row R l + i of the tile.
+// Loads are buffer loads: the descriptor moves with the step (scalar work) and
+// each lane's byte offsets inside a step are computed once. They need 4-byte
+// alignment only, so every leading dimension and size takes this path. Tiles
+// that cross the edge of the output and the k-steps that cross the end of the
+// contraction load element by element, with an offset past the descriptor's
+// size (the hardware returns zero) for what lies outside; where whole loads lie
+// inside or outside, rows past the edge are read from inside instead.
+#pragma once
+
+#include "common.hpp"
+#include "gemm_kernel.hpp"
+#include "kernels.hpp"
+
+namespace dlvm {
+namespace gemm {
+
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+
+constexpr uint32_t kBufSize = 0x7fffff00u;  // bytes past a descriptor's base that offsets may reach
+constexpr uint32_t kBufOut = 0x80000000u;   // an offset outside every descriptor: reads zero
+constexpr int kWaveStep = 16;               // k of one step
+
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t wave_rsrc(const float* base) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(base), 0,
+                                           static_cast<int>(kBufSize), 0x00020000);
+}
+
+// R consecutive floats at byte offset `off` of the descriptor.
+template <int R>
+__device__ __forceinline__ void buf_load(float (&d)[R], __amdgpu_buffer_rsrc_t rs, uint32_t off) {
+  if constexpr (R == 4) {
+    const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(rs, static_cast<int>(off), 0, 0);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) d[e] = __uint_as_float(v[e]);
+  } else if constexpr (R == 2) {
+    const u32x2 v = __builtin_amdgcn_raw_buffer_load_b64(rs, static_cast<int>(off), 0, 0);
+    d[0] = __uint_as_float(v[0]);
+    d[1] = __uint_as_float(v[1]);
+  } else {
+    static_assert(R == 1, "1, 2 or 4 floats");
+    d[0] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs, static_cast<int>(off), 0, 0));
+  }
+}
+
+// One operand of a tile: R blocks of 16 rows from row r0 (of rlim).
+// KMAJ: P[r * ld + k]; else P[k * ld + r].
+template <bool KMAJ, int R>
+struct WaveOperand {
+  uint32_t off[KMAJ ? R : 4];  // byte offsets inside a step from the tile's origin
+
+  // Rows past `rows` (rows left in the operand from the tile's first) are read
+  // from one inside: they only reach outputs that are not stored.
+  __device__ __forceinline__ void init(int64_t ld, int lane, int64_t rows) {
+    const int l = lane & 15, g = lane >> 4;
+#pragma unroll
+    for (int i = 0; i < (KMAJ ? R : 4); ++i) {
+      if constexpr (KMAJ) {
+        const int64_t r = 16 * i + l < rows ? 16 * i + l : 0;
+        off[i] = static_cast<uint32_t>((r * ld + 4 * g) * 4);
+      } else {
+        const int64_t r = R * l < rows ? R * l : 0;
+        off[i] = static_cast<uint32_t>(((4 * g + i) * ld + r) * 4);
+      }
+    }
+  }
+
+  // Values f[e][i] of instruction e, block i for the step whose first k lies at
+  // `P` (the tile's origin row). All of it lies inside the operand.
+  __device__ __forceinline__ void load(float (&f)[4][R], const float* P) const {
+    const __amdgpu_buffer_rsrc_t rs = wave_rsrc(P);
+    if constexpr (KMAJ) {
+#pragma unroll
+      for (int i = 0; i < R; ++i) {
+        float t[4];
+        buf_load<4>(t, rs, off[i]);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) f[e][i] = t[e];
+      }
+    } else {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) buf_load<R>(f[e], rs, off[e]);
+    }
+  }
+
+  // The same element by element: rows from `rows` on (rows left in the operand
+  // from the tile's first) and k from `ks` on (k left) read as zero.
+  __device__ __forceinline__ void load_edge(float (&f)[4][R], const float* P, int64_t ld, int lane,
+                                            int64_t rows, int64_t ks) const {
+    const __amdgpu_buffer_rsrc_t rs = wave_rsrc(P);
+    const int l = lane & 15, g = lane >> 4;
+#pragma unroll
+    for (int i = 0; i < R; ++i) {
+      const int r = KMAJ ? 16 * i + l : R * l + i;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int k = 4 * g + e;
+        const uint32_t o = static_cast<uint32_t>((KMAJ ? r * ld + k : k * ld + r) * 4);
+        float t[1];
+        buf_load<1>(t, rs, r < rows && k < ks ? o : kBufOut);
+        f[e][i] = t[0];
+      }
+    }
+  }
+};
+
+// LDS bytes of one workgroup: the waves' partial tiles (rows padded by 16
+// bytes: the stores of a wave's four row groups fall into different banks) and
+// the partial column sums.
+template <int AB, int BB, int NW>
+constexpr int wave_smem_bytes() {
+  return NW * (16 * AB * (16 * BB + 4) + 16 * BB) * 4;
+}
+
+// One output tile (`tile` from split_slice) of a product, LDS at `smem`. EDGE:
+// the tile crosses the edge of the output; EA, EB: a load of R columns of a
+// row-contiguous operand would straddle that edge, so it goes element by element.
+template <bool AK, bool BKM, int AB, int BB, int NW, int DEPTH, int EPI, bool PH2, bool EDGE,
+          bool EA, bool EB>
+__device__ __forceinline__ void wave_gemm_body(const Params& p, int64_t m0, int64_t n0, int tm,
+                                               char* smem) {
+  constexpr int TM = 16 * AB, TN = 16 * BB, LD = TN + 4;
+  constexpr int THREADS = 64 * NW;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int l = lane & 15, g = lane >> 4;
+  float* const part = reinterpret_cast<float*>(smem);          // [NW][TM][LD]
+  float* const cpart = part + NW * TM * LD;                    // [NW][TN]
+
+  // Outputs of this thread: element tid + j * THREADS of the tile, row by row.
+  // What their epilogue reads is loaded now, behind the contraction.
+  constexpr int PER = (TM * TN + THREADS - 1) / THREADS;
+  static_assert(TM * TN % THREADS == 0 || PER == 1, "whole outputs per thread, or at most one");
+  constexpr bool AHEAD = PER <= 2;
+  float pre_b[AHEAD ? PER : 1], pre_g[AHEAD ? PER : 1], pre_r[AHEAD ? PER : 1];
+  const float* const aux = static_cast<const float*>(p.aux);
+  const float* const res = static_cast<const float*>(p.residual);
+  const float* const bias = static_cast<const float*>(p.bias);
+  const bool use_aux = EPI == EPI_DACT && p.act != ACT_NONE;
+  const bool use_res = EPI == EPI_DACT && res != nullptr;
+  auto fetch = [&](int j, float& b, float& gr, float& r) {
+    const int o = tid + j * THREADS;
+    const int64_t row = m0 + o / TN, col = n0 + o % TN;
+    const bool in = o < TM * TN && (!EDGE || (row < p.M && col < p.N));
+    b = EPI == EPI_STORE && bias != nullptr && in && col < p.nvec ? bias[col] : 0.0f;
+    gr = use_aux && in ? aux[row * p.ldc + col] : 0.0f;
+    r = use_res && in ? res[row * p.ldc + col] : 0.0f;
+  };
+  if constexpr (AHEAD) {
+#pragma unroll
+    for (int j = 0; j < PER; ++j) fetch(j, pre_b[j], pre_g[j], pre_r[j]);
+  }
+
+  // Steps: the whole ones of both phases in order, shared out over the waves;
+  // what is left of phase 1 goes to the first wave, of phase 2 to the last.
+  const int64_t K1 = PH2 ? p.K1 : p.K;
+  const int nf1 = static_cast<int>(K1 / kWaveStep);
+  const int nf = PH2 ? nf1 + static_cast<int>((p.K - K1) / kWaveStep) : nf1;
+  const int s0 = static_cast<int>(static_cast<int64_t>(nf) * wave / NW);
+  const int s1 = static_cast<int>(static_cast<int64_t>(nf) * (wave + 1) / NW);
+  const int64_t tail1 = PH2 ? K1 - static_cast<int64_t>(nf1) * kWaveStep : 0;
+  const int64_t tail2 = PH2 ? p.K - K1 - static_cast<int64_t>(nf - nf1) * kWaveStep
+                            : p.K - static_cast<int64_t>(nf) * kWaveStep;
+
+  // Origin of a step: the tile's first row (or column) at its first k.
+  const float* const A = static_cast<const float*>(p.A);
+  const float* const B = static_cast<const float*>(p.B);
+  const float* const A2 = static_cast<const float*>(p.A2);
+  auto a_at = [&](int s, int64_t& ld) {
+    const bool ph2 = PH2 && s >= nf1;
+    ld = ph2 ? p.lda2 : p.lda;
+    const float* a = ph2 ? A2 : A;
+    const int64_t k = static_cast<int64_t>(ph2 ? s - nf1 : s) * kWaveStep;
+    return AK ? a + m0 * ld + k : a + k * ld + m0;
+  };
+  auto b_at = [&](int s) {
+    const int64_t k = PH2 && s >= nf1 ? K1 + static_cast<int64_t>(s - nf1) * kWaveStep
+                                      : static_cast<int64_t>(s) * kWaveStep;
+    return BKM ? B + n0 * p.ldb + k : B + k * p.ldb + n0;
+  };
+
+  WaveOperand<AK, AB> oa, oa2;
+  WaveOperand<BKM, BB> ob;
+  oa.init(p.lda, lane, p.M - m0);
+  if constexpr (PH2) oa2.init(p.lda2, lane, p.M - m0);
+  ob.init(p.ldb, lane, p.N - n0);
+
+  f32x4 acc[AB][BB];
+#pragma unroll
+  for (int i = 0; i < AB; ++i)
+#pragma unroll
+    for (int j = 0; j < BB; ++j) acc[i][j] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+  float cs[BB];
+#pragma unroll
+  for (int j = 0; j < BB; ++j) cs[j] = 0.0f;
+  const bool do_colsum = EPI == EPI_DW && p.colsum != nullptr && tm == 0;
+
+  float a[DEPTH][4][AB], b[DEPTH][4][BB];
+  auto load = [&](int d, int s) {
+    int64_t ld;
+    const float* pa = a_at(s, ld);
+    if constexpr (EA)
+      oa.load_edge(a[d], pa, ld, lane, p.M - m0, kWaveStep);
+    else if (PH2 && s >= nf1)
+      oa2.load(a[d], pa);
+    else
+      oa.load(a[d], pa);
+    if constexpr (EB)
+      ob.load_edge(b[d], b_at(s), p.ldb, lane, p.N - n0, kWaveStep);
+    else
+      ob.load(b[d], b_at(s));
+  };
+  auto multiply = [&](const float (&fa)[4][AB], const float (&fb)[4][BB]) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+#pragma unroll
+      for (int i = 0; i < AB; ++i)
+#pragma unroll
+        for (int j = 0; j < BB; ++j)
+          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(fa[e][i], fb[e][j], acc[i][j], 0, 0, 0);
+    if constexpr (EPI == EPI_DW) {
+      if (do_colsum) {
+#pragma unroll
+        for (int j = 0; j < BB; ++j) cs[j] += (fb[0][j] + fb[1][j]) + (fb[2][j] + fb[3][j]);
+      }
+    }
+  };
+
+  // A partial step (fewer than 16 k left of a phase), its loads first of all.
+  const bool t1 = PH2 && tail1 > 0 && wave == 0;
+  const bool t2 = tail2 > 0 && wave == NW - 1;
+  float ta[4][AB], tb[4][BB];
+  if (t1 || t2) {
+    const int64_t k = t1 ? static_cast<int64_t>(nf1) * kWaveStep
+                         : static_cast<int64_t>(PH2 ? nf - nf1 : nf) * kWaveStep;
+    const bool second = PH2 && t2;
+    const int64_t ld = second ? p.lda2 : p.lda, kb = second ? K1 + k : k;
+    const float* src = second ? A2 : A;
+    const int64_t left = t1 ? tail1 : tail2;
+    oa.load_edge(ta, AK ? src + m0 * ld + k : src + k * ld + m0, ld, lane, p.M - m0, left);
+    ob.load_edge(tb, BKM ? B + n0 * p.ldb + kb : B + kb * p.ldb + n0, p.ldb, lane, p.N - n0, left);
+  }
+
+  if (s1 > s0) {
+    // (past the wave's last step the last one is loaded again: a static number of loads in flight)
+#pragma unroll
+    for (int d = 0; d < DEPTH; ++d) load(d, s0 + d < s1 ? s0 + d : s1 - 1);
+    __builtin_amdgcn_sched_barrier(0);
+    int s = s0;
+    for (; s + DEPTH < s1; s += DEPTH) {
+#pragma unroll
+      for (int d = 0; d < DEPTH; ++d) {
+        multiply(a[d], b[d]);
+        load(d, s + d + DEPTH < s1 ? s + d + DEPTH : s1 - 1);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+#pragma unroll
+    for (int d = 0; d < DEPTH; ++d)
+      if (s + d < s1) multiply(a[d], b[d]);
+  }
+  if (t1 || t2) multiply(ta, tb);
+
+  // Partial tiles to LDS in row-major order. Accumulator register r of block
+  // (i, j) holds the block's row 4 g + r and column l.
+  float* const mine = part + wave * TM * LD;
+#pragma unroll
+  for (int i = 0; i < AB; ++i)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int row = AK ? 16 * i + 4 * g + r : AB * (4 * g + r) + i;
+      if constexpr (BKM || BB == 1) {
+#pragma unroll
+        for (int j = 0; j < BB; ++j) mine[row * LD + 16 * j + l] = acc[i][j][r];
+      } else if constexpr (BB == 2) {
+        *reinterpret_cast<float2*>(mine + row * LD + 2 * l) = make_float2(acc[i][0][r], acc[i][1][r]);
+      } else {
+        *reinterpret_cast<float4*>(mine + row * LD + 4 * l) =
+            make_float4(acc[i][0][r], acc[i][1][r], acc[i][2][r], acc[i][3][r]);
+      }
+    }
+  if constexpr (EPI == EPI_DW) {
+    if (do_colsum) {
+      // the four k groups of the wave (fixed order), then the waves below
+#pragma unroll
+      for (int j = 0; j < BB; ++j) {
+        cs[j] += __shfl_xor(cs[j], 16, 64);
+        cs[j] += __shfl_xor(cs[j], 32, 64);
+        if (g == 0) cpart[wave * TN + (BKM ? 16 * j + l : BB * l + j)] = cs[j];
+      }
+    }
+  }
+  __syncthreads();
+
+  float* const C = static_cast<float*>(p.C);
+#pragma unroll
+  for (int j = 0; j < PER; ++j) {
+    const int o = tid + j * THREADS;
+    if (PER == 1 && o >= TM * TN) break;
+    const int rr = o / TN, cc = o % TN;
+    const int64_t row = m0 + rr, col = n0 + cc;
+    float v = part[rr * LD + cc];
+#pragma unroll
+    for (int w = 1; w < NW; ++w) v += part[w * TM * LD + rr * LD + cc];
+    if (EDGE && (row >= p.M || col >= p.N)) continue;
+    float bv, gv, rv;
+    if constexpr (AHEAD) {
+      bv = pre_b[j]; gv = pre_g[j]; rv = pre_r[j];
+    } else {
+      fetch(j, bv, gv, rv);
+    }
+    if constexpr (EPI == EPI_STORE) {
+      v = apply_act(p.act, p.alpha * v + bv);
+    } else if constexpr (EPI == EPI_DACT) {
+      if (p.res_pre) v += rv;
+      if (use_aux) v *= act_grad_from_output(p.act, gv);
+      if (!p.res_pre) v += rv;
+    }
+    C[row * p.ldc + col] = v;
+  }
+  if constexpr (EPI == EPI_DW) {
+    if (do_colsum && tid < TN && n0 + tid < p.nvec) {
+      float t = cpart[tid];
+#pragma unroll
+      for (int w = 1; w < NW; ++w) t += cpart[w * TN + tid];
+      p.colsum[n0 + tid] = t;
+    }
+  }
+}
+
+template <bool AK, bool BKM, int AB, int BB, int NW, int DEPTH, int EPI, bool PH2 = false>
+__device__ __forceinline__ void wave_gemm_tile(const Params& p, int tile, char* smem) {
+  int tm, tn;
+  tile_of(tile, p.tiles_m, p.tiles_n, tm, tn);
+  const int64_t m0 = static_cast<int64_t>(tm) * (16 * AB);
+  const int64_t n0 = static_cast<int64_t>(tn) * (16 * BB);
+  if (m0 + 16 * AB <= p.M && n0 + 16 * BB <= p.N) {
+    wave_gemm_body<AK, BKM, AB, BB, NW, DEPTH, EPI, PH2, false, false, false>(p, m0, n0, tm, smem);
+  } else {
+    constexpr bool CA = !AK && AB > 1, CB = !BKM && BB > 1;  // loads of several columns
+    const bool sa = CA && m0 + 16 * AB > p.M && (p.M - m0) % AB != 0;
+    const bool sb = CB && n0 + 16 * BB > p.N && (p.N - n0) % BB != 0;
+    if ((CA || CB) && (sa || sb))
+      wave_gemm_body<AK, BKM, AB, BB, NW, DEPTH, EPI, PH2, true, CA, CB>(p, m0, n0, tm, smem);
+    else
+      wave_gemm_body<AK, BKM, AB, BB, NW, DEPTH, EPI, PH2, true, false, false>(p, m0, n0, tm, smem);
+  }
+}
+
+template <bool AK, bool BKM, int AB, int BB, int NW, int DEPTH, int EPI, bool PH2>
+__global__ __launch_bounds__(64 * NW) void dlvm_gemm_wave_kernel(Params p) {
+  __shared__ __attribute__((aligned(16))) char smem[wave_smem_bytes<AB, BB, NW>()];
+  const int tile = split_slice<float, AK, BKM>(p, static_cast<int>(blockIdx.x));
+  // (a k-slice of a split two-phase product lies in one phase)
+  if (PH2 && p.splits <= 1)
+    wave_gemm_tile<AK, BKM, AB, BB, NW, DEPTH, EPI, PH2>(p, tile, smem);
+  else
+    wave_gemm_tile<AK, BKM, AB, BB, NW, DEPTH, EPI, false>(p, tile, smem);
+}
+
+// The two adjoint products of one dense layer in one launch (blocks [0, n1):
+// TN wrt the weights, the rest: NT wrt the input), as dlvm_gemm_pair_kernel;
+// the two may use different tiles.
+template <int AB1, int BB1, int D1, int AB2, int BB2, int D2, int NW>
+__global__ __launch_bounds__(64 * NW) void dlvm_gemm_wave_pair_kernel(Params p1, Params p2, int n1) {
+  constexpr int S1 = wave_smem_bytes<AB1, BB1, NW>(), S2 = wave_smem_bytes<AB2, BB2, NW>();
+  __shared__ __attribute__((aligned(16))) char smem[S1 > S2 ? S1 : S2];
+  const int b = static_cast<int>(blockIdx.x);
+  if (b < n1) {
+    const int tile = split_slice<float, false, false>(p1, b);
+    wave_gemm_tile<false, false, AB1, BB1, NW, D1, EPI_DW>(p1, tile, smem);
+  } else {
+    const int tile = split_slice<float, true, true>(p2, b - n1);
+    wave_gemm_tile<true, true, AB2, BB2, NW, D2, EPI_DACT>(p2, tile, smem);
+  }
+}
+
+}  // namespace gemm
+}  // namespace dlvm

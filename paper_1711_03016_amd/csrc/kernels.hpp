@@ -75,6 +75,8 @@ struct GemmDesc {
   // loss term (sum of e^2) per wavefront of each tile (chain_partials of them);
   // inv_n is the seed 1 / (M N) of the mean. Never split.
   bool chain_epilogue;
+  bool chain_product;  // the product of a chain network (chain in its epilogue or after it):
+                       // planned the same either way, so that both give the same bits
   void* C2;
   float* partials;
   float inv_n;
@@ -124,7 +126,7 @@ int64_t chain_partials(const GemmPlan& plan);
 hipError_t launch_gemm(const GemmDesc& d, const GemmPlan& plan, hipStream_t s);
 
 // The two adjoint products of one layer (tn: wrt the weights, nt: wrt the
-// input) can run as one launch when planned on the same configuration.
+// input) can run as one launch when planned on configurations that have a paired kernel.
 bool pairable(const GemmDesc& tn, const GemmPlan& ptn, const GemmDesc& nt, const GemmPlan& pnt);
 hipError_t launch_gemm_pair(const GemmDesc& tn, const GemmPlan& ptn, const GemmDesc& nt,
                             const GemmPlan& pnt, hipStream_t s);
