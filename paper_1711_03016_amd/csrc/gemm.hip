@@ -111,13 +111,12 @@ bool xl_phases_ok(const GemmDesc& d) {
          d.N <= d.ldb;
 }
 
-// The float32 kernel that loads its fragments from global memory (configurations
-// 6-9): any size and alignment; the byte offsets inside a step (up to 64 rows)
-// stay below 2^31.
+// The kernel that loads its fragments from global memory (configurations 6-9): any
+// size and alignment; the byte offsets inside a step (up to 64 rows) stay below 2^31.
 bool wave_config(int cfg) { return cfg >= 6 && cfg <= 9; }
 bool wave_ok(const GemmDesc& d) {
   const int64_t lim = int64_t(1) << 22;
-  return d.dtype == F32 && !d.chain_product && d.lda <= lim && d.ldb <= lim &&
+  return !d.chain_product && d.mask == nullptr && d.lda <= lim && d.ldb <= lim &&
          (!two_phase(d) || d.lda2 <= lim);
 }
 
@@ -160,16 +159,38 @@ double estimate_f32(const GemmDesc& d, const TileShape& t, int64_t slots, int64_
   return fixed + rounds * mfma * over;
 }
 
+// The same for a bf16 product on the waves that share the contraction (6-9): per
+// round a fixed part (first loads, partial tiles through LDS) and its operands at
+// the bytes per cycle measured for each layout, on 64 x 256 x 356 to
+// 4096 x 1024 x 1024; times 1.5 where rows start anywhere (2049-element rows and
+// the like). The estimates of the direct-to-LDS tiles, which a product with aligned
+// rows is compared with, leave out the launch and are about 1.35 times too low where
+// the two meet (1024 x 1024 x 4096 wrt the weights in four slices on 19: 38,700
+// against 59,500 measured, 25 us on either kernel).
+double estimate_wave_bf16(const GemmDesc& d, const TileShape& t, int64_t slots, int64_t kc, bool aligned) {
+  static const double fix[] = {1400.0, 2000.0, 2500.0, 10000.0};
+  static const double rate[4][3] = {  // NN, NT, TN
+      {18.0, 15.0, 11.0}, {15.0, 16.0, 15.0}, {16.0, 14.0, 17.0}, {16.0, 17.0, 24.0}};
+  const int i = t.cfg - 6;
+  const double rounds = double(ceil_div(slots, kComputeUnits));
+  const double bytes = double(t.bm + t.bn) * double(kc) * 2.0;
+  const double c = rounds * (fix[i] + bytes / rate[i][static_cast<int>(d.layout)]);
+  return aligned ? c / 1.35 : 2000.0 + 1.5 * c;
+}
+
 // Clock cycles one configuration needs: rounds of tiles over the compute
 // units, each tile bound by its matrix-core work or its operand traffic, plus
-// the reduction of a split product.
-double estimate(const GemmDesc& d, const TileShape& t, int splits) {
+// the reduction of a split product. `aligned`: the direct-to-LDS bf16 tiles can
+// run the product.
+double estimate(const GemmDesc& d, const TileShape& t, int splits, bool aligned) {
   const int64_t tiles = ceil_div(d.M, t.bm) * ceil_div(d.N, t.bn);
   const int64_t kc = splits > 1 ? slice_k(d.K, splits) : d.K;
   const int64_t slices = ceil_div(d.K, kc);
   double c;
   if (d.dtype == F32) {
     c = estimate_f32(d, t, tiles * slices, kc);
+  } else if (wave_config(t.cfg)) {
+    c = estimate_wave_bf16(d, t, tiles * slices, kc, aligned);
   } else {
     const double rate = kRateBF16 * t.eff_bf16;
     const double flops = 2.0 * t.bm * t.bn * double(kc);
@@ -181,6 +202,7 @@ double estimate(const GemmDesc& d, const TileShape& t, int splits) {
     }
     per_tile += kTileFixed;
     c = double(ceil_div(tiles * slices, kComputeUnits)) * per_tile;
+    if (!aligned) c += 6000.0;  // (launch: the waves' estimate counts it for such products)
   }
   if (slices > 1) c += kLaunch + double(slices + 1) * double(d.M) * double(d.N) * 4.0 / kHbmBytesPerClock;
   return c;
@@ -300,7 +322,7 @@ GemmPlan choose(const GemmDesc& d, bool assume_aligned, int64_t capacity, int fo
         if (split_need(d, sp) > capacity) break;
       }
       if (forcing && sp != fsplits) continue;
-      const double e = estimate(d, t, sp);
+      const double e = estimate(d, t, sp, can_async);
       if (best == nullptr || e < best_t * 0.97) {  // prefer earlier (larger) tiles, fewer splits
         best = &t;
         best_s = sp;
@@ -376,36 +398,24 @@ int64_t split_ws_elems(const GemmDesc& d) {
 
 namespace {
 
-// Whether 16-byte loads are legal for each operand of the register-staged
-// kernel. 16-byte loads need 16-byte aligned rows (ld a multiple of the vector
-// width). Along k a chunk must lie entirely inside or outside [0, K) (k
-// padding would reach every output); along m or n a chunk that starts inside
-// the extent stays inside its row, and its elements past the extent only reach
-// outputs that are not stored.
+// Whether each operand of the register-staged kernel can be loaded 16 bytes at a
+// time: every row (in each phase of the contraction) holds at least one chunk.
 void vector_ok(const GemmDesc& d, bool& va, bool& vb) {
   const int vw = d.dtype == F32 ? 4 : 8;
-  va = aligned16(d.A) && d.lda % vw == 0;
-  vb = aligned16(d.B) && d.ldb % vw == 0;
-  switch (d.layout) {
-    case Layout::NN: va = va && d.K % vw == 0; break;
-    case Layout::NT: va = va && d.K % vw == 0; vb = vb && d.K % vw == 0; break;
-    case Layout::TN: break;
-  }
-  // Two phases: every chunk along k inside or outside each phase's extent,
-  // and 16-byte rows of A2.
-  if (d.A2 != nullptr) {
-    va = va && phases_ok(d, vw);
-    if (d.layout != Layout::NN) vb = vb && d.K1 % vw == 0;
-  }
+  const int64_t kmin = d.A2 != nullptr ? std::min(d.K1, d.K - d.K1) : d.K;
+  va = (d.layout == Layout::TN ? d.M : kmin) >= vw;
+  vb = (d.layout == Layout::NT ? kmin : d.N) >= vw;
 }
 
-// Whether every operand row of a float32 product starts on 16 bytes and every
-// 16-byte load of the direct-to-LDS kernel lies inside or outside the operand.
+// Whether every row of both operands of a float32 product starts on 16 bytes and
+// every 16-byte chunk along k lies inside or outside each phase (a chunk along m or
+// n that starts inside the extent stays inside its padded row; its elements past
+// the extent only reach outputs that are not stored).
 bool vec16(const GemmDesc& d) {
-  bool va, vb;
-  vector_ok(d, va, vb);
-  if (two_phase(d) && d.K1 % 4 != 0) return false;
-  return va && vb;
+  const bool ak = d.layout != Layout::TN, bk = d.layout == Layout::NT;
+  if (!aligned16(d.A) || d.lda % 4 != 0 || !aligned16(d.B) || d.ldb % 4 != 0) return false;
+  if ((ak || bk) && d.K % 4 != 0) return false;
+  return !two_phase(d) || (phases_ok(d, 4) && d.K1 % 4 == 0);
 }
 
 // Whether a launch loads its operands through buffer descriptors (and needs
@@ -482,9 +492,9 @@ hipError_t launch_gemm(const GemmDesc& d, const GemmPlan& pl, hipStream_t s) {
     return hipErrorInvalidValue;
   const gemm::Params p = make_params(d, pl);
   const unsigned grid = grid_of(pl);
-  if (wave_config(pl.cfg)) return gemm::launch_wave(p, d.layout, pl.cfg, grid, s);
   if (f32_config(pl.cfg)) return gemm::launch_f32(p, d.layout, pl.cfg, grid, vec16(d), s);
   const int out = pl.splits > 1 ? F32 : d.out_dtype;  // split slices: float32 partials
+  if (wave_config(pl.cfg)) return gemm::launch_wave(p, d.layout, d.dtype, out, pl.cfg, grid, s);
   switch (d.layout) {
     case Layout::NN: return gemm::launch_nn(p, d.dtype, out, pl.cfg, grid, va, vb, s);
     case Layout::NT: return gemm::launch_nt(p, d.dtype, out, pl.cfg, grid, va, vb, s);
@@ -514,11 +524,12 @@ hipError_t launch_gemm_pair(const GemmDesc& tn, const GemmPlan& ptn, const GemmD
   if (nt.mask != nullptr && (!mask_ok(nt, pnt) || !aligned16(nt.mask))) return hipErrorInvalidValue;
   const gemm::Params p1 = make_params(tn, ptn), p2 = make_params(nt, pnt);
   const unsigned n1 = grid_of(ptn);
-  if (tn.dtype == F32)
-    return gemm::launch_f32_pair(p1, p2, static_cast<int>(n1), n1 + grid_of(pnt), ptn.cfg, pnt.cfg,
-                                 vec16(tn) && vec16(nt), s);
-  return gemm::launch_pair(p1, p2, static_cast<int>(n1), n1 + grid_of(pnt), tn.dtype,
-                           nt.out_dtype, ptn.cfg, s);
+  const int nb = static_cast<int>(n1);
+  const unsigned grid = n1 + grid_of(pnt);
+  if (wave_config(ptn.cfg))
+    return gemm::launch_wave_pair(p1, p2, nb, grid, tn.dtype, nt.out_dtype, ptn.cfg, pnt.cfg, s);
+  if (f32_config(ptn.cfg)) return gemm::launch_f32_pair(p1, p2, nb, grid, ptn.cfg, vec16(tn) && vec16(nt), s);
+  return gemm::launch_pair(p1, p2, nb, grid, nt.out_dtype, ptn.cfg, s);
 }
 
 }  // namespace dlvm

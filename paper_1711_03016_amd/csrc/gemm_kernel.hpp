@@ -200,6 +200,37 @@ __device__ __forceinline__ uint32_t perm_b32(uint32_t hi, uint32_t lo, uint32_t 
 // unconditionally from a clamped, always valid address and its validity is
 // kept aside, so no branch and no consumer of the loaded registers sits
 // between the loads and the matrix-core work that hides their latency.
+//
+// The 16-byte loads ask for the alignment of one element only, so rows may start
+// anywhere; a chunk that crosses the end of its row (a K or N that is not a
+// multiple of the vector width) is loaded from the row's last whole chunk and
+// shifted into place, zeros behind it, in store(). Element loads are left to
+// rows shorter than one chunk. Measured on bf16 rows of odd lengths against element
+// loads: 1000 x 500 x 784 45 -> 14 us (64 x 64 tile), 10071 x 2090 x 3424 about
+// 1,400 -> 298 us (128 x 128 tile).
+struct __attribute__((packed, aligned(2))) Chunk16 {
+  uint32_t w[4];
+};
+__device__ __forceinline__ uint4 load_chunk(const void* p) {
+  const Chunk16 c = *static_cast<const Chunk16*>(p);
+  return make_uint4(c.w[0], c.w[1], c.w[2], c.w[3]);
+}
+// The 128 bits of w moved down by `bits` (16 .. 112), zeros above.
+__device__ __forceinline__ void shift_chunk(uint32_t (&w)[4], int bits) {
+  uint64_t lo = (static_cast<uint64_t>(w[1]) << 32) | w[0], hi = (static_cast<uint64_t>(w[3]) << 32) | w[2];
+  if (bits >= 64) {
+    lo = hi;
+    hi = 0;
+    bits -= 64;
+  }
+  if (bits > 0) {
+    lo = (lo >> bits) | (hi << (64 - bits));
+    hi >>= bits;
+  }
+  w[0] = static_cast<uint32_t>(lo); w[1] = static_cast<uint32_t>(lo >> 32);
+  w[2] = static_cast<uint32_t>(hi); w[3] = static_cast<uint32_t>(hi >> 32);
+}
+
 template <typename T, bool KMAJ, int ROWS, int THREADS, bool VEC, int KSEG>
 struct TileLoader {
   static constexpr int VW = Elem<T>::VW;
@@ -210,6 +241,9 @@ struct TileLoader {
   static_assert(NLOAD <= 32, "validity mask");
   uint32_t raw[NLOAD][4];
   uint32_t ok = 0;  // bit i: load i lies inside the operand
+  static constexpr int NSHIFT = KMAJ ? 1 : PER_THREAD;
+  // bits to move the chunks of task i by (KMAJ: one value, as a thread's tasks share their chunk)
+  int shift[NSHIFT] = {};
 
   // Task q -> (row or row block, chunk). K-contiguous operands put the chunk
   // index fastest (consecutive lanes read consecutive 16 bytes of a row);
@@ -244,9 +278,13 @@ struct TileLoader {
         const int64_t gr = r0 + rb;
         const int64_t gk = k0 + c * VW;
         if constexpr (VEC) {
+          static_assert(THREADS % CH == 0, "a thread's tasks share their chunk");
           const bool in = gr < rlim && gk < klim;
           ok |= in ? (1u << i) : 0u;
-          put(i, *reinterpret_cast<const uint4*>(in ? P + gr * ld + gk : P));
+          const int over = static_cast<int>(gk + VW - klim);  // elements past the row's end
+          const int64_t ks = over > 0 ? klim - VW : gk;
+          if (i == 0) shift[0] = over > 0 ? over * static_cast<int>(8 * sizeof(T)) : 0;
+          put(i, load_chunk(in ? P + gr * ld + ks : P));
         } else {
           T e[VW];
 #pragma unroll
@@ -259,15 +297,16 @@ struct TileLoader {
       } else {
         const int64_t gr = r0 + rb * VW;
         const int64_t gk = k0 + c * VW;
+        const int over = VEC ? static_cast<int>(gr + VW - rlim) : 0;  // elements past the row's end
+        const int64_t rs = over > 0 ? rlim - VW : gr;
+        if constexpr (VEC)
+          shift[i] = over > 0 && over < VW ? over * static_cast<int>(8 * sizeof(T)) : 0;
 #pragma unroll
         for (int kk = 0; kk < VW; ++kk) {
           if constexpr (VEC) {
-            // The whole 16-byte run lies inside row gk+kk (ld is a multiple of
-            // the vector width); elements past rlim reach only outputs that
-            // are not stored.
             const bool in = gr < rlim && gk + kk < klim;
             ok |= in ? (1u << (i * VW + kk)) : 0u;
-            put(i * VW + kk, *reinterpret_cast<const uint4*>(in ? P + (gk + kk) * ld + gr : P));
+            put(i * VW + kk, load_chunk(in ? P + (gk + kk) * ld + rs : P));
           } else {
             T e[VW];
 #pragma unroll
@@ -295,9 +334,12 @@ struct TileLoader {
       char* base = lds + (c / kChunks) * SEG_BYTES + (c % kChunks) * 16;
       if constexpr (KMAJ) {
         const bool o = (ok >> i) & 1u;
-        *reinterpret_cast<uint4*>(base + rb * kRowStride) =
-            make_uint4(o ? raw[i][0] : 0u, o ? raw[i][1] : 0u, o ? raw[i][2] : 0u,
-                       o ? raw[i][3] : 0u);
+        uint32_t w[4] = {o ? raw[i][0] : 0u, o ? raw[i][1] : 0u, o ? raw[i][2] : 0u,
+                         o ? raw[i][3] : 0u};
+        if constexpr (VEC) {
+          if (shift[0] > 0 && o) shift_chunk(w, shift[0]);
+        }
+        *reinterpret_cast<uint4*>(base + rb * kRowStride) = make_uint4(w[0], w[1], w[2], w[3]);
       } else {
         uint32_t w[VW][4];  // w[kk] = elements (k = kk, r = 0 .. VW-1) of the block
 #pragma unroll
@@ -306,6 +348,12 @@ struct TileLoader {
           const bool o = (ok >> n) & 1u;
           w[kk][0] = o ? raw[n][0] : 0u; w[kk][1] = o ? raw[n][1] : 0u;
           w[kk][2] = o ? raw[n][2] : 0u; w[kk][3] = o ? raw[n][3] : 0u;
+        }
+        if constexpr (VEC) {
+          if (shift[i] > 0) {
+#pragma unroll
+            for (int kk = 0; kk < VW; ++kk) shift_chunk(w[kk], shift[i]);
+          }
         }
         uint32_t t[VW][4];  // t[j] = row r = j of the block, its VW k values
         if constexpr (sizeof(T) == 4) {
@@ -724,9 +772,9 @@ hipError_t launch_f32_far(const Params& p, int cfg, unsigned grid, hipStream_t s
   return hipGetLastError();
 }
 
-// Float32 products of the waves that share the contraction (gemm_wave.hpp,
-// configurations 6-9). One translation unit.
-hipError_t launch_wave(const Params& p, Layout layout, int cfg, unsigned grid, hipStream_t s);
+// Products of the waves that share the contraction (gemm_wave.hpp, configurations 6-9).
+hipError_t launch_wave(const Params& p, Layout layout, int dtype, int out_dtype, int cfg, unsigned grid,
+                       hipStream_t s);
 // Large float32 products staged in LDS by direct loads (gemm_f32.hpp,
 // configurations 20-22); vec: 16-byte loads.
 hipError_t launch_f32(const Params& p, Layout layout, int cfg, unsigned grid, bool vec, hipStream_t s);
@@ -734,10 +782,12 @@ hipError_t launch_f32(const Params& p, Layout layout, int cfg, unsigned grid, bo
 // The two adjoint products of a layer (TN wrt the weights, NT wrt the input)
 // in one launch, for the configurations (of the two) pair_config accepts.
 bool pair_config(int dtype, int cfg_tn, int cfg_nt);
-hipError_t launch_f32_pair(const Params& p1, const Params& p2, int n1, unsigned grid, int cfg_tn,
-                           int cfg_nt, bool vec, hipStream_t s);
-hipError_t launch_pair(const Params& p1, const Params& p2, int n1, unsigned grid, int dtype,
-                       int out_dtype2, int cfg, hipStream_t s);
+hipError_t launch_pair(const Params& p1, const Params& p2, int n1, unsigned grid, int out_dtype2, int cfg,
+                       hipStream_t s);
+hipError_t launch_wave_pair(const Params& p1, const Params& p2, int n1, unsigned grid, int dtype,
+                            int out_dtype2, int cfg_tn, int cfg_nt, hipStream_t s);
+hipError_t launch_f32_pair(const Params& p1, const Params& p2, int n1, unsigned grid, int cfg, bool vec,
+                           hipStream_t s);
 
 // Per-layout entry points (one translation unit each).
 hipError_t launch_nn(const Params& p, int dtype, int out_dtype, int cfg, unsigned grid, bool va,

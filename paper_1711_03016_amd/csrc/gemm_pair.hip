@@ -7,12 +7,13 @@ namespace dlvm {
 namespace gemm {
 
 bool pair_config(int dtype, int cfg_tn, int cfg_nt) {
-  if (dtype == F32) {
-    // (6, 7 and 8 have the same number of waves, so any two of them share a launch)
-    const bool w1 = cfg_tn >= 6 && cfg_tn <= 8, w2 = cfg_nt >= 6 && cfg_nt <= 8;
-    return (w1 && w2) || (cfg_tn == cfg_nt && (cfg_tn == 9 || (cfg_tn >= 20 && cfg_tn <= 22)));
-  }
-  return cfg_tn == cfg_nt && (cfg_tn == 3 || cfg_tn == 10 || cfg_tn == 12);
+  // (6, 7 and 8 have the same number of waves, so any two of them share a launch)
+  const bool w1 = cfg_tn >= 6 && cfg_tn <= 8, w2 = cfg_nt >= 6 && cfg_nt <= 8;
+  if (w1 && w2) return true;
+  if (cfg_tn != cfg_nt) return false;
+  if (cfg_tn == 9) return true;
+  if (dtype == F32) return cfg_tn >= 20 && cfg_tn <= 22;
+  return cfg_tn == 3 || cfg_tn == 10 || cfg_tn == 12;
 }
 
 namespace {
@@ -39,8 +40,8 @@ hipError_t launch_async_pair(const Params& p1, const Params& p2, int n1, unsigne
 
 }  // namespace
 
-hipError_t launch_pair(const Params& p1, const Params& p2, int n1, unsigned grid, int dtype,
-                       int out_dtype2, int cfg, hipStream_t s) {
+hipError_t launch_pair(const Params& p1, const Params& p2, int n1, unsigned grid, int out_dtype2, int cfg,
+                       hipStream_t s) {
   if (cfg >= kAsyncFirst) {
     if (out_dtype2 == F32) return launch_async_pair<float>(p1, p2, n1, grid, cfg, s);
     return launch_async_pair<bf16_t>(p1, p2, n1, grid, cfg, s);

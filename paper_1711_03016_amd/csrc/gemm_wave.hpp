@@ -1,39 +1,44 @@
-// Float32 dense-layer products whose waves load their matrix-core fragments
-// straight from global memory and share the contraction between them.
+// Dense-layer products whose waves load their matrix-core fragments straight
+// from global memory and share the contraction between them.
 //
 // Same products and fused epilogues as gemm_kernel.hpp (NN forward, NT adjoint
-// wrt the input, TN adjoint wrt the weights). A workgroup of NW waves owns one
-// tile of 16 AB x 16 BB outputs; every wave computes the whole tile over its own
-// contiguous range of k-steps (16 k each), and the NW partial tiles are added
-// in wave order through LDS at the end, where the epilogue runs.
+// wrt the input, TN adjoint wrt the weights), float32 or bf16 operands. A workgroup
+// of NW waves owns one tile of 16 AB x 16 BB outputs; every wave computes the whole
+// tile over its own contiguous range of k-steps (16 k of float32, 32 of bf16), and
+// the NW partial tiles are added in wave order through LDS at the end, where the
+// epilogue runs.
 //
 // What bounds these products is not arithmetic: with a few hundred tiles each
 // compute unit has one, and its time is the latency of reaching the operands.
 // Staged through LDS, every k-stage cost a memory round trip and a barrier
-// (about 3,500 cycles per 128 k). Here the loads of DEPTH steps are in flight
-// per wave, no barrier stands between the first load and the one reduction,
-// and the operands cross no LDS. Measured back to back on 256 x 512 outputs
-// (rotating operands): K 784 12.5 -> 5.4 us, K 512 10 -> 4.1 us; 64 x 256 x 356
-// (a recurrent cell) 9.2 -> 2.8 us; 512 x 512 x 256 wrt the weights 8 -> 4.1 us.
+// (about 3,500 cycles per 128 k of float32). Here the loads of DEPTH steps are in
+// flight per wave, no barrier stands between the first load and the one reduction,
+// and the operands cross no LDS. Measured back to back in float32 (rotating
+// operands): 256 x 512 x 784 12.7 -> 5.8 us, 256 x 512 x 512 9.3 -> 4.3;
+// 64 x 256 x 356 (a recurrent cell) 8.1 -> 3.3; 512 x 512 x 256 wrt the weights
+// 6.8 -> 4.2. In bf16: 1000 x 500 x 784 (rows of 500) 45 -> 9.6, 4096 x 10 x 1024
+// 11.3 -> 5.0, 1024 x 16 x 4096 wrt the weights 11.4 (in slices, with their sum) -> 7.3.
 //
-// Fragments without a transpose. v_mfma_f32_16x16x4_f32 wants, in lane
-// 16 g + l, the value of row (or column) l at the g-th of its 4 k. Both
-// operands may use any assignment of k to (instruction, g) as long as they use
-// the same one, and rows may be assigned to lanes in any order that the store
-// undoes, so:
-//   k-contiguous operand: one 16-byte load per 16-row block, lane (g, l)
-//     taking k = 4 g .. 4 g + 3 of row l; value e feeds instruction e.
-//   row-contiguous operand (its k strided in memory): for each e one load of
-//     the 16 * R columns of row k = 4 g + e, lane l taking columns R l .. R l + R - 1
-//     (R = AB or BB, a 4 R byte load); value i belongs to block i, whose row l
-//     is thus row R l + i of the tile.
-// Loads are buffer loads: the descriptor moves with the step (scalar work) and
-// each lane's byte offsets inside a step are computed once. They need 4-byte
-// alignment only, so every leading dimension and size takes this path. Tiles
-// that cross the edge of the output and the k-steps that cross the end of the
-// contraction load element by element, with an offset past the descriptor's
-// size (the hardware returns zero) for what lies outside; where whole loads lie
-// inside or outside, rows past the edge are read from inside instead.
+// Fragments without LDS. v_mfma_f32_16x16x4_f32 wants, in lane 16 g + l, the value
+// of row (or column) l at the g-th of its 4 k; v_mfma_f32_16x16x32_bf16 the 8
+// values at k = 8 g .. 8 g + 7. Both operands may use any assignment of k to
+// (instruction, g) as long as they use the same one, and rows may be assigned to
+// lanes in any order that the store undoes, so:
+//   k-contiguous operand: one 16-byte load per 16-row block, lane (g, l) taking
+//     the 4 (8) k at 4 g (8 g) of row l; float32 value e feeds instruction e.
+//   row-contiguous operand (its k strided in memory): for each e of those k one
+//     load of the 16 R columns of that k's row, lane l taking columns
+//     R l .. R l + R - 1 (R = AB or BB); value i belongs to block i, whose row l is
+//     thus row R l + i of the tile. bf16 values of consecutive k are paired by byte
+//     permutes when they are multiplied.
+// Loads go through a descriptor or base that moves with the step (scalar work) and
+// byte offsets inside a step that each lane computes once. They ask for the
+// alignment of one element only, so every leading dimension and size takes this
+// path. Rows past the edge of the output are read from one inside (they reach only
+// outputs that are not stored); where a load of R columns would straddle that edge,
+// and in the k-step that crosses the end of the contraction, values are loaded one
+// by one, with an offset past the descriptor's size (the hardware returns zero) for
+// what lies outside.
 #pragma once
 
 #include "common.hpp"
@@ -48,10 +53,11 @@ typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 
 constexpr uint32_t kBufSize = 0x7fffff00u;  // bytes past a descriptor's base that offsets may reach
 constexpr uint32_t kBufOut = 0x80000000u;   // an offset outside every descriptor: reads zero
-constexpr int kWaveStep = 16;               // k of one step
 
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t wave_rsrc(const float* base) {
-  return __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(base), 0,
+template <typename T> constexpr int wave_step() { return sizeof(T) == 4 ? 16 : 32; }  // k of one step
+
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t wave_rsrc(const void* base) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0,
                                            static_cast<int>(kBufSize), 0x00020000);
 }
 
@@ -72,31 +78,49 @@ __device__ __forceinline__ void buf_load(float (&d)[R], __amdgpu_buffer_rsrc_t r
   }
 }
 
-// One operand of a tile: R blocks of 16 rows from row r0 (of rlim).
-// KMAJ: P[r * ld + k]; else P[k * ld + r].
-template <bool KMAJ, int R>
-struct WaveOperand {
-  uint32_t off[KMAJ ? R : 4];  // byte offsets inside a step from the tile's origin
+// One operand of a tile: R blocks of 16 rows. KMAJ: P[r * ld + k]; else P[k * ld + r].
+// Lane (g, l) loads the E values at k = E g .. of a step.
+template <typename T, bool KMAJ, int R>
+struct WaveOffsets {
+  static constexpr int E = wave_step<T>() / 4;
+  uint32_t off[KMAJ ? R : E];  // byte offsets inside a step from the tile's origin
 
   // Rows past `rows` (rows left in the operand from the tile's first) are read
   // from one inside: they only reach outputs that are not stored.
   __device__ __forceinline__ void init(int64_t ld, int lane, int64_t rows) {
     const int l = lane & 15, g = lane >> 4;
 #pragma unroll
-    for (int i = 0; i < (KMAJ ? R : 4); ++i) {
+    for (int i = 0; i < (KMAJ ? R : E); ++i) {
       if constexpr (KMAJ) {
         const int64_t r = 16 * i + l < rows ? 16 * i + l : 0;
-        off[i] = static_cast<uint32_t>((r * ld + 4 * g) * 4);
+        off[i] = static_cast<uint32_t>((r * ld + E * g) * static_cast<int64_t>(sizeof(T)));
       } else {
         const int64_t r = R * l < rows ? R * l : 0;
-        off[i] = static_cast<uint32_t>(((4 * g + i) * ld + r) * 4);
+        off[i] = static_cast<uint32_t>(((E * g + i) * ld + r) * static_cast<int64_t>(sizeof(T)));
       }
     }
   }
+  // Byte offset of value e of block i, or one outside every descriptor where
+  // the row lies past `rows` or its k past `ks` (counted from the origin).
+  __device__ __forceinline__ static uint32_t edge(int i, int e, int64_t ld, int lane, int64_t rows,
+                                                  int64_t ks) {
+    const int l = lane & 15, g = lane >> 4;
+    const int r = KMAJ ? 16 * i + l : R * l + i, k = E * g + e;
+    const int64_t o = (KMAJ ? r * ld + k : k * ld + r) * static_cast<int64_t>(sizeof(T));
+    return r < rows && k < ks ? static_cast<uint32_t>(o) : kBufOut;
+  }
+};
 
-  // Values f[e][i] of instruction e, block i for the step whose first k lies at
-  // `P` (the tile's origin row). All of it lies inside the operand.
-  __device__ __forceinline__ void load(float (&f)[4][R], const float* P) const {
+template <typename T, bool KMAJ, int R> struct WaveOperand;
+
+// float32: value e of block i feeds instruction e of the step.
+template <bool KMAJ, int R>
+struct WaveOperand<float, KMAJ, R> : WaveOffsets<float, KMAJ, R> {
+  struct Regs { float v[4][R]; };
+  using WaveOffsets<float, KMAJ, R>::off;
+
+  // The step whose first k lies at `P` (the tile's origin row), all inside the operand.
+  __device__ __forceinline__ void load(Regs& f, const float* P) const {
     const __amdgpu_buffer_rsrc_t rs = wave_rsrc(P);
     if constexpr (KMAJ) {
 #pragma unroll
@@ -104,31 +128,84 @@ struct WaveOperand {
         float t[4];
         buf_load<4>(t, rs, off[i]);
 #pragma unroll
-        for (int e = 0; e < 4; ++e) f[e][i] = t[e];
+        for (int e = 0; e < 4; ++e) f.v[e][i] = t[e];
       }
     } else {
 #pragma unroll
-      for (int e = 0; e < 4; ++e) buf_load<R>(f[e], rs, off[e]);
+      for (int e = 0; e < 4; ++e) buf_load<R>(f.v[e], rs, off[e]);
     }
   }
-
-  // The same element by element: rows from `rows` on (rows left in the operand
-  // from the tile's first) and k from `ks` on (k left) read as zero.
-  __device__ __forceinline__ void load_edge(float (&f)[4][R], const float* P, int64_t ld, int lane,
+  // The same value by value, zeros for rows from `rows` and k from `ks` on.
+  __device__ __forceinline__ void load_edge(Regs& f, const float* P, int64_t ld, int lane,
                                             int64_t rows, int64_t ks) const {
     const __amdgpu_buffer_rsrc_t rs = wave_rsrc(P);
-    const int l = lane & 15, g = lane >> 4;
 #pragma unroll
-    for (int i = 0; i < R; ++i) {
-      const int r = KMAJ ? 16 * i + l : R * l + i;
+    for (int i = 0; i < R; ++i)
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        const int k = 4 * g + e;
-        const uint32_t o = static_cast<uint32_t>((KMAJ ? r * ld + k : k * ld + r) * 4);
         float t[1];
-        buf_load<1>(t, rs, r < rows && k < ks ? o : kBufOut);
-        f[e][i] = t[0];
+        buf_load<1>(t, rs, this->edge(i, e, ld, lane, rows, ks));
+        f.v[e][i] = t[0];
       }
+  }
+};
+
+// bf16: k-contiguous, the 8 values of block i in v[i]; row-contiguous, the R values
+// at each k in w[e] (two to a word).
+template <bool KMAJ, int R>
+struct WaveOperand<bf16_t, KMAJ, R> : WaveOffsets<bf16_t, KMAJ, R> {
+  static constexpr int W = R > 1 ? R / 2 : 1;
+  struct Regs { uint32_t w[KMAJ ? R : 8][KMAJ ? 4 : W]; };
+  using WaveOffsets<bf16_t, KMAJ, R>::off;
+  struct __attribute__((packed, aligned(2))) Words { uint32_t w[KMAJ ? 4 : W]; };
+
+  __device__ __forceinline__ void load(Regs& f, const bf16_t* P) const {
+    const char* const base = reinterpret_cast<const char*>(P);
+#pragma unroll
+    for (int i = 0; i < (KMAJ ? R : 8); ++i) {
+      if constexpr (!KMAJ && R == 1) {
+        f.w[i][0] = *reinterpret_cast<const bf16_t*>(base + off[i]);
+      } else {
+        const Words t = *reinterpret_cast<const Words*>(base + off[i]);
+#pragma unroll
+        for (int q = 0; q < (KMAJ ? 4 : W); ++q) f.w[i][q] = t.w[q];
+      }
+    }
+  }
+  __device__ __forceinline__ void load_edge(Regs& f, const bf16_t* P, int64_t ld, int lane,
+                                            int64_t rows, int64_t ks) const {
+    const __amdgpu_buffer_rsrc_t rs = wave_rsrc(P);
+    auto one = [&](int i, int e) {
+      return static_cast<uint32_t>(static_cast<uint16_t>(__builtin_amdgcn_raw_buffer_load_b16(
+          rs, static_cast<int>(this->edge(i, e, ld, lane, rows, ks)), 0, 0)));
+    };
+    if constexpr (KMAJ) {
+#pragma unroll
+      for (int i = 0; i < R; ++i)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) f.w[i][q] = one(i, 2 * q) | (one(i, 2 * q + 1) << 16);
+    } else {
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        if constexpr (R == 1) {
+          f.w[e][0] = one(0, e);
+        } else {
+#pragma unroll
+          for (int q = 0; q < W; ++q) f.w[e][q] = one(2 * q, e) | (one(2 * q + 1, e) << 16);
+        }
+      }
+    }
+  }
+  // The 8 values of block i.
+  __device__ __forceinline__ static bf16x8 frag(const Regs& f, int i) {
+    if constexpr (KMAJ) {
+      return __builtin_bit_cast(bf16x8, make_uint4(f.w[i][0], f.w[i][1], f.w[i][2], f.w[i][3]));
+    } else {
+      uint32_t t[4];
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        t[q] = perm_b32(f.w[2 * q + 1][i >> 1], f.w[2 * q][i >> 1], (i & 1) ? 0x07060302u : 0x05040100u);
+      return __builtin_bit_cast(bf16x8, make_uint4(t[0], t[1], t[2], t[3]));
     }
   }
 };
@@ -144,12 +221,12 @@ constexpr int wave_smem_bytes() {
 // One output tile (`tile` from split_slice) of a product, LDS at `smem`. EDGE:
 // the tile crosses the edge of the output; EA, EB: a load of R columns of a
 // row-contiguous operand would straddle that edge, so it goes element by element.
-template <bool AK, bool BKM, int AB, int BB, int NW, int DEPTH, int EPI, bool PH2, bool EDGE,
-          bool EA, bool EB>
+template <typename T, typename TO, bool AK, bool BKM, int AB, int BB, int NW, int DEPTH, int EPI,
+          bool PH2, bool EDGE, bool EA, bool EB>
 __device__ __forceinline__ void wave_gemm_body(const Params& p, int64_t m0, int64_t n0, int tm,
                                                char* smem) {
   constexpr int TM = 16 * AB, TN = 16 * BB, LD = TN + 4;
-  constexpr int THREADS = 64 * NW;
+  constexpr int THREADS = 64 * NW, STEP = wave_step<T>();
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l = lane & 15, g = lane >> 4;
@@ -162,18 +239,18 @@ __device__ __forceinline__ void wave_gemm_body(const Params& p, int64_t m0, int6
   static_assert(TM * TN % THREADS == 0 || PER == 1, "whole outputs per thread, or at most one");
   constexpr bool AHEAD = PER <= 2;
   float pre_b[AHEAD ? PER : 1], pre_g[AHEAD ? PER : 1], pre_r[AHEAD ? PER : 1];
-  const float* const aux = static_cast<const float*>(p.aux);
-  const float* const res = static_cast<const float*>(p.residual);
-  const float* const bias = static_cast<const float*>(p.bias);
+  const T* const aux = static_cast<const T*>(p.aux);
+  const TO* const res = static_cast<const TO*>(p.residual);
+  const T* const bias = static_cast<const T*>(p.bias);
   const bool use_aux = EPI == EPI_DACT && p.act != ACT_NONE;
   const bool use_res = EPI == EPI_DACT && res != nullptr;
   auto fetch = [&](int j, float& b, float& gr, float& r) {
     const int o = tid + j * THREADS;
     const int64_t row = m0 + o / TN, col = n0 + o % TN;
     const bool in = o < TM * TN && (!EDGE || (row < p.M && col < p.N));
-    b = EPI == EPI_STORE && bias != nullptr && in && col < p.nvec ? bias[col] : 0.0f;
-    gr = use_aux && in ? aux[row * p.ldc + col] : 0.0f;
-    r = use_res && in ? res[row * p.ldc + col] : 0.0f;
+    b = EPI == EPI_STORE && bias != nullptr && in && col < p.nvec ? load_as_f32<T>(bias + col) : 0.0f;
+    gr = use_aux && in ? load_as_f32<T>(aux + row * p.ldc + col) : 0.0f;
+    r = use_res && in ? load_as_f32<TO>(res + row * p.ldc + col) : 0.0f;
   };
   if constexpr (AHEAD) {
 #pragma unroll
@@ -183,33 +260,35 @@ __device__ __forceinline__ void wave_gemm_body(const Params& p, int64_t m0, int6
   // Steps: the whole ones of both phases in order, shared out over the waves;
   // what is left of phase 1 goes to the first wave, of phase 2 to the last.
   const int64_t K1 = PH2 ? p.K1 : p.K;
-  const int nf1 = static_cast<int>(K1 / kWaveStep);
-  const int nf = PH2 ? nf1 + static_cast<int>((p.K - K1) / kWaveStep) : nf1;
+  const int nf1 = static_cast<int>(K1 / STEP);
+  const int nf = PH2 ? nf1 + static_cast<int>((p.K - K1) / STEP) : nf1;
   const int s0 = static_cast<int>(static_cast<int64_t>(nf) * wave / NW);
   const int s1 = static_cast<int>(static_cast<int64_t>(nf) * (wave + 1) / NW);
-  const int64_t tail1 = PH2 ? K1 - static_cast<int64_t>(nf1) * kWaveStep : 0;
-  const int64_t tail2 = PH2 ? p.K - K1 - static_cast<int64_t>(nf - nf1) * kWaveStep
-                            : p.K - static_cast<int64_t>(nf) * kWaveStep;
+  const int64_t tail1 = PH2 ? K1 - static_cast<int64_t>(nf1) * STEP : 0;
+  const int64_t tail2 = PH2 ? p.K - K1 - static_cast<int64_t>(nf - nf1) * STEP
+                            : p.K - static_cast<int64_t>(nf) * STEP;
 
   // Origin of a step: the tile's first row (or column) at its first k.
-  const float* const A = static_cast<const float*>(p.A);
-  const float* const B = static_cast<const float*>(p.B);
-  const float* const A2 = static_cast<const float*>(p.A2);
+  const T* const A = static_cast<const T*>(p.A);
+  const T* const B = static_cast<const T*>(p.B);
+  const T* const A2 = static_cast<const T*>(p.A2);
   auto a_at = [&](int s, int64_t& ld) {
     const bool ph2 = PH2 && s >= nf1;
     ld = ph2 ? p.lda2 : p.lda;
-    const float* a = ph2 ? A2 : A;
-    const int64_t k = static_cast<int64_t>(ph2 ? s - nf1 : s) * kWaveStep;
+    const T* a = ph2 ? A2 : A;
+    const int64_t k = static_cast<int64_t>(ph2 ? s - nf1 : s) * STEP;
     return AK ? a + m0 * ld + k : a + k * ld + m0;
   };
   auto b_at = [&](int s) {
-    const int64_t k = PH2 && s >= nf1 ? K1 + static_cast<int64_t>(s - nf1) * kWaveStep
-                                      : static_cast<int64_t>(s) * kWaveStep;
+    const int64_t k = PH2 && s >= nf1 ? K1 + static_cast<int64_t>(s - nf1) * STEP
+                                      : static_cast<int64_t>(s) * STEP;
     return BKM ? B + n0 * p.ldb + k : B + k * p.ldb + n0;
   };
 
-  WaveOperand<AK, AB> oa, oa2;
-  WaveOperand<BKM, BB> ob;
+  using OA = WaveOperand<T, AK, AB>;
+  using OB = WaveOperand<T, BKM, BB>;
+  OA oa, oa2;
+  OB ob;
   oa.init(p.lda, lane, p.M - m0);
   if constexpr (PH2) oa2.init(p.lda2, lane, p.M - m0);
   ob.init(p.ldb, lane, p.N - n0);
@@ -224,33 +303,59 @@ __device__ __forceinline__ void wave_gemm_body(const Params& p, int64_t m0, int6
   for (int j = 0; j < BB; ++j) cs[j] = 0.0f;
   const bool do_colsum = EPI == EPI_DW && p.colsum != nullptr && tm == 0;
 
-  float a[DEPTH][4][AB], b[DEPTH][4][BB];
+  typename OA::Regs a[DEPTH];
+  typename OB::Regs b[DEPTH];
   auto load = [&](int d, int s) {
     int64_t ld;
-    const float* pa = a_at(s, ld);
+    const T* pa = a_at(s, ld);
     if constexpr (EA)
-      oa.load_edge(a[d], pa, ld, lane, p.M - m0, kWaveStep);
+      oa.load_edge(a[d], pa, ld, lane, p.M - m0, STEP);
     else if (PH2 && s >= nf1)
       oa2.load(a[d], pa);
     else
       oa.load(a[d], pa);
     if constexpr (EB)
-      ob.load_edge(b[d], b_at(s), p.ldb, lane, p.N - n0, kWaveStep);
+      ob.load_edge(b[d], b_at(s), p.ldb, lane, p.N - n0, STEP);
     else
       ob.load(b[d], b_at(s));
   };
-  auto multiply = [&](const float (&fa)[4][AB], const float (&fb)[4][BB]) {
+  auto multiply = [&](const typename OA::Regs& ra, const typename OB::Regs& rb) {
+    if constexpr (sizeof(T) == 4) {
 #pragma unroll
-    for (int e = 0; e < 4; ++e)
+      for (int e = 0; e < 4; ++e)
+#pragma unroll
+        for (int i = 0; i < AB; ++i)
+#pragma unroll
+          for (int j = 0; j < BB; ++j)
+            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(ra.v[e][i], rb.v[e][j], acc[i][j], 0, 0, 0);
+      if constexpr (EPI == EPI_DW) {
+        if (do_colsum) {
+#pragma unroll
+          for (int j = 0; j < BB; ++j) cs[j] += (rb.v[0][j] + rb.v[1][j]) + (rb.v[2][j] + rb.v[3][j]);
+        }
+      }
+    } else {
+      bf16x8 fa[AB], fb[BB];
+#pragma unroll
+      for (int i = 0; i < AB; ++i) fa[i] = OA::frag(ra, i);
+#pragma unroll
+      for (int j = 0; j < BB; ++j) fb[j] = OB::frag(rb, j);
 #pragma unroll
       for (int i = 0; i < AB; ++i)
 #pragma unroll
         for (int j = 0; j < BB; ++j)
-          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(fa[e][i], fb[e][j], acc[i][j], 0, 0, 0);
-    if constexpr (EPI == EPI_DW) {
-      if (do_colsum) {
+          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[i], fb[j], acc[i][j], 0, 0, 0);
+      if constexpr (EPI == EPI_DW) {
+        if (do_colsum) {
 #pragma unroll
-        for (int j = 0; j < BB; ++j) cs[j] += (fb[0][j] + fb[1][j]) + (fb[2][j] + fb[3][j]);
+          for (int j = 0; j < BB; ++j) {
+            const uint4 x = __builtin_bit_cast(uint4, fb[j]);
+            const uint32_t q[4] = {x.x, x.y, x.z, x.w};
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+              cs[j] += __uint_as_float(q[e] << 16) + __uint_as_float(q[e] & 0xffff0000u);
+          }
+        }
       }
     }
   };
@@ -258,13 +363,14 @@ __device__ __forceinline__ void wave_gemm_body(const Params& p, int64_t m0, int6
   // A partial step (fewer than 16 k left of a phase), its loads first of all.
   const bool t1 = PH2 && tail1 > 0 && wave == 0;
   const bool t2 = tail2 > 0 && wave == NW - 1;
-  float ta[4][AB], tb[4][BB];
+  typename OA::Regs ta;
+  typename OB::Regs tb;
   if (t1 || t2) {
-    const int64_t k = t1 ? static_cast<int64_t>(nf1) * kWaveStep
-                         : static_cast<int64_t>(PH2 ? nf - nf1 : nf) * kWaveStep;
+    const int64_t k = t1 ? static_cast<int64_t>(nf1) * STEP
+                         : static_cast<int64_t>(PH2 ? nf - nf1 : nf) * STEP;
     const bool second = PH2 && t2;
     const int64_t ld = second ? p.lda2 : p.lda, kb = second ? K1 + k : k;
-    const float* src = second ? A2 : A;
+    const T* src = second ? A2 : A;
     const int64_t left = t1 ? tail1 : tail2;
     oa.load_edge(ta, AK ? src + m0 * ld + k : src + k * ld + m0, ld, lane, p.M - m0, left);
     ob.load_edge(tb, BKM ? B + n0 * p.ldb + kb : B + kb * p.ldb + n0, p.ldb, lane, p.N - n0, left);
@@ -321,7 +427,7 @@ __device__ __forceinline__ void wave_gemm_body(const Params& p, int64_t m0, int6
   }
   __syncthreads();
 
-  float* const C = static_cast<float*>(p.C);
+  TO* const C = static_cast<TO*>(p.C);
 #pragma unroll
   for (int j = 0; j < PER; ++j) {
     const int o = tid + j * THREADS;
@@ -345,7 +451,7 @@ __device__ __forceinline__ void wave_gemm_body(const Params& p, int64_t m0, int6
       if (use_aux) v *= act_grad_from_output(p.act, gv);
       if (!p.res_pre) v += rv;
     }
-    C[row * p.ldc + col] = v;
+    C[row * p.ldc + col] = store_cast<TO>(v);
   }
   if constexpr (EPI == EPI_DW) {
     if (do_colsum && tid < TN && n0 + tid < p.nvec) {
@@ -357,50 +463,52 @@ __device__ __forceinline__ void wave_gemm_body(const Params& p, int64_t m0, int6
   }
 }
 
-template <bool AK, bool BKM, int AB, int BB, int NW, int DEPTH, int EPI, bool PH2 = false>
+template <typename T, typename TO, bool AK, bool BKM, int AB, int BB, int NW, int DEPTH, int EPI,
+          bool PH2 = false>
 __device__ __forceinline__ void wave_gemm_tile(const Params& p, int tile, char* smem) {
   int tm, tn;
   tile_of(tile, p.tiles_m, p.tiles_n, tm, tn);
   const int64_t m0 = static_cast<int64_t>(tm) * (16 * AB);
   const int64_t n0 = static_cast<int64_t>(tn) * (16 * BB);
   if (m0 + 16 * AB <= p.M && n0 + 16 * BB <= p.N) {
-    wave_gemm_body<AK, BKM, AB, BB, NW, DEPTH, EPI, PH2, false, false, false>(p, m0, n0, tm, smem);
+    wave_gemm_body<T, TO, AK, BKM, AB, BB, NW, DEPTH, EPI, PH2, false, false, false>(p, m0, n0, tm, smem);
   } else {
     constexpr bool CA = !AK && AB > 1, CB = !BKM && BB > 1;  // loads of several columns
     const bool sa = CA && m0 + 16 * AB > p.M && (p.M - m0) % AB != 0;
     const bool sb = CB && n0 + 16 * BB > p.N && (p.N - n0) % BB != 0;
     if ((CA || CB) && (sa || sb))
-      wave_gemm_body<AK, BKM, AB, BB, NW, DEPTH, EPI, PH2, true, CA, CB>(p, m0, n0, tm, smem);
+      wave_gemm_body<T, TO, AK, BKM, AB, BB, NW, DEPTH, EPI, PH2, true, CA, CB>(p, m0, n0, tm, smem);
     else
-      wave_gemm_body<AK, BKM, AB, BB, NW, DEPTH, EPI, PH2, true, false, false>(p, m0, n0, tm, smem);
+      wave_gemm_body<T, TO, AK, BKM, AB, BB, NW, DEPTH, EPI, PH2, true, false, false>(p, m0, n0, tm, smem);
   }
 }
 
-template <bool AK, bool BKM, int AB, int BB, int NW, int DEPTH, int EPI, bool PH2>
+template <typename T, typename TO, bool AK, bool BKM, int AB, int BB, int NW, int DEPTH, int EPI,
+          bool PH2>
 __global__ __launch_bounds__(64 * NW) void dlvm_gemm_wave_kernel(Params p) {
   __shared__ __attribute__((aligned(16))) char smem[wave_smem_bytes<AB, BB, NW>()];
-  const int tile = split_slice<float, AK, BKM>(p, static_cast<int>(blockIdx.x));
+  const int tile = split_slice<T, AK, BKM>(p, static_cast<int>(blockIdx.x));
   // (a k-slice of a split two-phase product lies in one phase)
   if (PH2 && p.splits <= 1)
-    wave_gemm_tile<AK, BKM, AB, BB, NW, DEPTH, EPI, PH2>(p, tile, smem);
+    wave_gemm_tile<T, TO, AK, BKM, AB, BB, NW, DEPTH, EPI, PH2>(p, tile, smem);
   else
-    wave_gemm_tile<AK, BKM, AB, BB, NW, DEPTH, EPI, false>(p, tile, smem);
+    wave_gemm_tile<T, TO, AK, BKM, AB, BB, NW, DEPTH, EPI, false>(p, tile, smem);
 }
 
 // The two adjoint products of one dense layer in one launch (blocks [0, n1):
 // TN wrt the weights, the rest: NT wrt the input), as dlvm_gemm_pair_kernel;
 // the two may use different tiles.
-template <int AB1, int BB1, int D1, int AB2, int BB2, int D2, int NW>
+template <typename T, typename TO2, int AB1, int BB1, int D1, int AB2, int BB2, int D2, int NW>
 __global__ __launch_bounds__(64 * NW) void dlvm_gemm_wave_pair_kernel(Params p1, Params p2, int n1) {
   constexpr int S1 = wave_smem_bytes<AB1, BB1, NW>(), S2 = wave_smem_bytes<AB2, BB2, NW>();
   __shared__ __attribute__((aligned(16))) char smem[S1 > S2 ? S1 : S2];
   const int b = static_cast<int>(blockIdx.x);
   if (b < n1) {
-    const int tile = split_slice<float, false, false>(p1, b);
-    wave_gemm_tile<false, false, AB1, BB1, NW, D1, EPI_DW>(p1, tile, smem);
+    const int tile = split_slice<T, false, false>(p1, b);
+    wave_gemm_tile<T, float, false, false, AB1, BB1, NW, D1, EPI_DW>(p1, tile, smem);
   } else {
-    const int tile = split_slice<float, true, true>(p2, b - n1);
-    wave_gemm_tile<true, true, AB2, BB2, NW, D2, EPI_DACT>(p2, tile, smem);
+    const int tile = split_slice<T, true, true>(p2, b - n1);
+    wave_gemm_tile<T, TO2, true, true, AB2, BB2, NW, D2, EPI_DACT>(p2, tile, smem);
   }
 }
 
