@@ -318,6 +318,10 @@ LaunchInfo elementwise_info(const char* name, int64_t rows, int64_t cols, double
   return i;
 }
 
+std::string tile_name(const dlvm::GemmPlan& pl) {
+  return std::to_string(pl.bm) + "x" + std::to_string(pl.bn) + "c" + std::to_string(pl.cfg);
+}
+
 // Every launch of the model-level calls goes through one Launcher. With a
 // plan vector it only records what it would launch (no pointer is touched);
 // otherwise it enqueues the launch on the caller's stream, bracketed by the
@@ -332,11 +336,12 @@ class Launcher {
   Launcher(const Launcher&) = delete;
   Launcher& operator=(const Launcher&) = delete;
 
-  template <class F>
-  dlvm_status run(LaunchInfo info, F&& launch, const char* what) {
+  // `describe` gives the launch's LaunchInfo; only a dry run asks for it.
+  template <class D, class F>
+  dlvm_status run(D&& describe, F&& launch, const char* what) {
     const int32_t idx = index_++;
     if (plan_ != nullptr) {
-      plan_->push_back(std::move(info));
+      plan_->push_back(describe());
       return DLVM_OK;
     }
     if (m_ == nullptr) {  // a call without a model handle: nothing to record
@@ -357,12 +362,8 @@ class Launcher {
   }
 
   dlvm_status gemm(const GemmDesc& d) {
-    const dlvm::GemmPlan pl = dlvm::plan_gemm(d);
-    LaunchInfo info = gemm_info(d);
-    info.name += "_" + std::to_string(pl.bm) + "x" + std::to_string(pl.bn) + "c" + std::to_string(pl.cfg);
-    if (pl.splits > 1) info.name += "s" + std::to_string(pl.splits);
-    dlvm_status st = run(std::move(info), [&](hipStream_t s) { return dlvm::launch_gemm(d, pl, s); },
-                         "gemm launch");
+    dlvm::GemmPlan pl{};
+    const dlvm_status st = gemm_raw(d, pl);
     if (st != DLVM_OK) return st;
     return reduce_split(d, pl);
   }
@@ -380,7 +381,7 @@ class Launcher {
       const double bytes = double(pl.splits) * mn * 4.0 + mn * eo +
                            (d.aux && d.act != DLVM_ACT_NONE ? mn * ei : 0.0) +
                            (d.residual ? mn * eo : 0.0) + (d.bias ? double(nv) * ei : 0.0);
-      return run(elementwise_info("split_epilogue", d.M, d.N, bytes),
+      return run([&] { return elementwise_info("split_epilogue", d.M, d.N, bytes); },
                  [&](hipStream_t s) {
                    return dlvm::launch_split_epilogue(
                        d.dtype, d.out_dtype, d.layout == Layout::NN ? 0 : 1, pl.splits, d.M, d.N,
@@ -392,7 +393,7 @@ class Launcher {
     const float* cs = d.split_ws + pl.splits * c_split;
     const double bytes = (double(pl.splits) + 1.0) * double(d.M) * double(d.N) * 4.0 +
                          (d.colsum ? (double(pl.splits) + 1.0) * double(nv) * 4.0 : 0.0);
-    return run(elementwise_info("splitk_reduce", d.M, d.N, bytes),
+    return run([&] { return elementwise_info("splitk_reduce", d.M, d.N, bytes); },
                [&](hipStream_t s) {
                  return dlvm::launch_splitk_reduce(pl.splits, d.M, d.N, d.ldc, d.split_ws, c_split,
                                                    static_cast<float*>(d.C), cs, nv, d.colsum, nv, s);
@@ -403,11 +404,14 @@ class Launcher {
   // One product without the reduction of its k-slices (the caller sums them).
   dlvm_status gemm_raw(const GemmDesc& d, dlvm::GemmPlan& pl) {
     pl = dlvm::plan_gemm(d);
-    LaunchInfo info = gemm_info(d);
-    info.name += "_" + std::to_string(pl.bm) + "x" + std::to_string(pl.bn) + "c" + std::to_string(pl.cfg);
-    if (pl.splits > 1) info.name += "s" + std::to_string(pl.splits);
-    return run(std::move(info), [&](hipStream_t s) { return dlvm::launch_gemm(d, pl, s); },
-               "gemm launch");
+    return run(
+        [&] {
+          LaunchInfo info = gemm_info(d);
+          info.name += "_" + tile_name(pl);
+          if (pl.splits > 1) info.name += "s" + std::to_string(pl.splits);
+          return info;
+        },
+        [&](hipStream_t s) { return dlvm::launch_gemm(d, pl, s); }, "gemm launch");
   }
 
   // A layer's two adjoint products (tn: wrt the weights, nt: wrt the input):
@@ -419,17 +423,18 @@ class Launcher {
       dlvm_status st = gemm(tn);
       return st != DLVM_OK ? st : gemm(nt);
     }
-    LaunchInfo a = gemm_info(tn), b = gemm_info(nt);
-    LaunchInfo info;
-    info.name = std::string("gemm_pair_") + (tn.dtype == DLVM_F32 ? "f32_" : "bf16_") +
-                std::to_string(p1.bm) + "x" + std::to_string(p1.bn) + "c" + std::to_string(p1.cfg) +
-                (p1.splits > 1 ? "s" + std::to_string(p1.splits) : std::string());
-    info.M = a.M; info.N = a.N; info.K = a.K;  // the product wrt the weights
-    info.flops = a.flops + b.flops;
-    info.bytes = a.bytes + b.bytes;
-    dlvm_status st = run(std::move(info),
-                         [&](hipStream_t s) { return dlvm::launch_gemm_pair(tn, p1, nt, p2, s); },
-                         "paired gemm launch");
+    dlvm_status st = run(
+        [&] {
+          const LaunchInfo a = gemm_info(tn), b = gemm_info(nt);
+          LaunchInfo info;
+          info.name = std::string("gemm_pair_") + (tn.dtype == DLVM_F32 ? "f32_" : "bf16_") + tile_name(p1) +
+                      (p1.splits > 1 ? "s" + std::to_string(p1.splits) : std::string());
+          info.M = a.M; info.N = a.N; info.K = a.K;  // the product wrt the weights
+          info.flops = a.flops + b.flops;
+          info.bytes = a.bytes + b.bytes;
+          return info;
+        },
+        [&](hipStream_t s) { return dlvm::launch_gemm_pair(tn, p1, nt, p2, s); }, "paired gemm launch");
     if (st != DLVM_OK) return st;
     return reduce_split(tn, p1);
   }
@@ -595,9 +600,38 @@ bool small_step_allowed() {
 dlvm_status plan_gradient(const dlvm_model* m, const void* params, const void* x,
                           const int32_t* labels, int64_t batch, float* loss, float* dparams,
                           float* dx, void* ws, Launcher& run) {
-  const WsLayout w = ws_layout(m, batch);
   const int L = m->L;
   const int dt = m->dtype;
+  // A small float32 network: the whole gradient in one workgroup (one launch).
+  dlvm::SmallNet sn{};  // (its flags lie at the workspace's start, as in every layout)
+  if (m->loss == DLVM_LOSS_SOFTMAX_CE && small_step_allowed() && m->dtype == DLVM_F32 &&
+      dlvm::small_net(L, m->widths.data(), m->acts.data(), m->offsets.data(), m->ldw.data(),
+                      batch, m->wrt_x != 0, sn)) {
+    auto describe = [&] {
+      double flops = 0.0, bytes = 0.0;
+      for (int l = 0; l < L; ++l) {
+        const double k = m->widths[l], n = m->widths[l + 1];
+        flops += 2.0 * batch * k * n * ((l > 0 || m->wrt_x) ? 3.0 : 2.0);
+        bytes += 8.0 * (k * n + n);  // parameters read, their gradient written
+      }
+      bytes += 4.0 * batch * (m->widths[0] + (m->wrt_x ? m->widths[0] : 0) + 1);
+      LaunchInfo info;
+      info.name = "small_step_f32";
+      info.M = batch; info.N = m->widths[L]; info.K = m->widths[0];
+      info.flops = flops;
+      info.bytes = bytes;
+      return info;
+    };
+    return run.run(describe,
+                   [&](hipStream_t s) {
+                     return dlvm::launch_small_step(sn, static_cast<const float*>(params),
+                                                    static_cast<const float*>(x), labels, loss,
+                                                    dparams, dx, at<int32_t>(ws, 0), m->gaps, s);
+                   },
+                   "small-network gradient launch");
+  }
+
+  const WsLayout w = ws_layout(m, batch);
   const double es = double(elem_size(dt));
   float* partials = at<float>(ws, w.partials);
   int32_t* bad = at<int32_t>(ws, w.bad);
@@ -610,7 +644,7 @@ dlvm_status plan_gradient(const dlvm_model* m, const void* params, const void* x
   const bool chain = m->loss == DLVM_LOSS_CHAIN8;
   const int32_t* badp = chain ? nullptr : bad;
   auto finalize = [&]() {
-    return run.run(elementwise_info("finalize", np, 1, 8.0 * np + 4.0),
+    return run.run([&] { return elementwise_info("finalize", np, 1, 8.0 * np + 4.0); },
                    [&](hipStream_t s) {
                      return dlvm::launch_finalize(partials, badp, np, scale, loss, flags, dparams,
                                                   m->gaps, s);
@@ -634,18 +668,21 @@ dlvm_status plan_gradient(const dlvm_model* m, const void* params, const void* x
       d.inv_n = scale;
       const dlvm::GemmPlan pl = dlvm::plan_gemm(d);
       np = static_cast<int>(dlvm::chain_partials(pl));
-      LaunchInfo info = gemm_info(d);
-      info.name = "gemm_nn_chain8_f32_" + std::to_string(pl.bm) + "x" + std::to_string(pl.bn) + "c" +
-                  std::to_string(pl.cfg);
-      info.bytes += 12.0 * double(batch) * double(N);  // x_skip read, zbar and xbar written
-      st = run.run(std::move(info), [&](hipStream_t s) { return dlvm::launch_gemm(d, pl, s); },
+      st = run.run(
+          [&] {
+            LaunchInfo info = gemm_info(d);
+            info.name = "gemm_nn_chain8_f32_" + tile_name(pl);
+            info.bytes += 12.0 * double(batch) * double(N);  // x_skip read, zbar and xbar written
+            return info;
+          },
+          [&](hipStream_t s) { return dlvm::launch_gemm(d, pl, s); },
                    "chain product launch");
     } else {
       GemmDesc zd = gemm_nn(dt, DLVM_F32, DLVM_ACT_NONE, batch, N, K, 1.0f, x, P(0), N, nullptr, z, N);
       zd.chain_product = true;
       if ((st = run.gemm(zd)) != DLVM_OK) return st;
       np = dlvm::chain8_partials(batch, N);
-      st = run.run(elementwise_info("chain8", batch, N, 16.0 * double(batch) * N + 4.0 * N),
+      st = run.run([&] { return elementwise_info("chain8", batch, N, 16.0 * double(batch) * N + 4.0 * N); },
                    [&](hipStream_t s) {
                      int n = 0;
                      return dlvm::launch_chain8(batch, N, z, static_cast<const float*>(P(1)),
@@ -663,32 +700,6 @@ dlvm_status plan_gradient(const dlvm_model* m, const void* params, const void* x
                                  nullptr, dx, dx);
     if ((st = run.gemm_pair(dw, dxd)) != DLVM_OK) return st;
     return finalize();
-  }
-
-  // A small float32 network: the whole gradient in one workgroup (one launch).
-  dlvm::SmallNet sn{};
-  if (small_step_allowed() && m->dtype == DLVM_F32 &&
-      dlvm::small_net(L, m->widths.data(), m->acts.data(), m->offsets.data(), m->ldw.data(),
-                      batch, m->wrt_x != 0, sn)) {
-    double flops = 0.0, bytes = 0.0;
-    for (int l = 0; l < L; ++l) {
-      const double k = m->widths[l], n = m->widths[l + 1];
-      flops += 2.0 * batch * k * n * ((l > 0 || m->wrt_x) ? 3.0 : 2.0);
-      bytes += 8.0 * (k * n + n);  // parameters read, their gradient written
-    }
-    bytes += 4.0 * batch * (m->widths[0] + (m->wrt_x ? m->widths[0] : 0) + 1);
-    LaunchInfo info;
-    info.name = "small_step_f32";
-    info.M = batch; info.N = m->widths[L]; info.K = m->widths[0];
-    info.flops = flops;
-    info.bytes = bytes;
-    return run.run(std::move(info),
-                   [&](hipStream_t s) {
-                     return dlvm::launch_small_step(sn, static_cast<const float*>(params),
-                                                    static_cast<const float*>(x), labels, loss,
-                                                    dparams, dx, flags, m->gaps, s);
-                   },
-                   "small-network gradient launch");
   }
 
   // Forward, keeping the layer outputs (every one, or the checkpoints and the
@@ -709,8 +720,8 @@ dlvm_status plan_gradient(const dlvm_model* m, const void* params, const void* x
   dlvm::GemmPlan hp{};
   if ((st = run.gemm_raw(head, hp)) != DLVM_OK) return st;
   if (hp.splits > 1) {
-    st = run.run(elementwise_info("split_softmax_xent", batch, C,
-                                  double(batch) * C * (4.0 * hp.splits + es) + 4.0 * batch),
+    st = run.run([&] { return elementwise_info("split_softmax_xent", batch, C,
+                                  double(batch) * C * (4.0 * hp.splits + es) + 4.0 * batch); },
                  [&](hipStream_t s) {
                    return dlvm::launch_split_softmax_xent(
                        dt, hp.splits, batch, C, head.split_ws, batch * C, C, P(2 * L - 1), labels,
@@ -719,7 +730,7 @@ dlvm_status plan_gradient(const dlvm_model* m, const void* params, const void* x
                  "softmax cross-entropy launch");
   } else {
     // (the kernel chosen decides how many loss partials it writes)
-    st = run.run(elementwise_info("softmax_xent", batch, C, double(batch) * C * (4.0 + es) + 4.0 * batch),
+    st = run.run([&] { return elementwise_info("softmax_xent", batch, C, double(batch) * C * (4.0 + es) + 4.0 * batch); },
                  [&](hipStream_t s) {
                    return dlvm::launch_softmax_xent(dt, batch, C, at<float>(ws, w.logits), labels,
                                                     scale, at<void>(ws, w.dz[L - 1]), ldc, partials,
@@ -747,14 +758,14 @@ dlvm_status plan_vjp(const dlvm_model* m, const void* params, const void* x, con
   dlvm_status st = DLVM_OK;
   if ((st = plan_hidden_forward(m, params, x, batch, ws, w, run)) != DLVM_OK) return st;
   const int64_t C = m->widths[L], ldc = m->ldw[L - 1];
-  st = run.run(elementwise_info("seed", batch, C, double(batch) * (4.0 * C + elem_size(dt) * ldc)),
+  st = run.run([&] { return elementwise_info("seed", batch, C, double(batch) * (4.0 * C + elem_size(dt) * ldc)); },
                [&](hipStream_t s) {
                  return dlvm::launch_seed(dt, batch, C, ldc, seed, at<void>(ws, w.dz[L - 1]), s);
                },
                "seed launch");
   if (st != DLVM_OK) return st;
   if ((st = plan_adjoint_layers(m, params, x, batch, dparams, dx, ws, w, run)) != DLVM_OK) return st;
-  return run.run(elementwise_info("zero_padding", 0, 1, 4.0 * m->param_count),
+  return run.run([&] { return elementwise_info("zero_padding", 0, 1, 4.0 * m->param_count); },
                  [&](hipStream_t s) {
                    return dlvm::launch_finalize(nullptr, nullptr, 0, 1.0f, nullptr, nullptr, dparams,
                                                 m->gaps, s);
@@ -777,7 +788,7 @@ dlvm_status plan_forward(const dlvm_model* m, const void* params, const void* x,
                                param_ptr(m, params, m->offsets[0]), N, nullptr, z, N))) != DLVM_OK)
       return st;
     const float* bias = static_cast<const float*>(param_ptr(m, params, m->offsets[1]));
-    return run.run(elementwise_info("chain8_forward", batch, N, 12.0 * double(batch) * N + 4.0 * N),
+    return run.run([&] { return elementwise_info("chain8_forward", batch, N, 12.0 * double(batch) * N + 4.0 * N); },
                    [&](hipStream_t s) {
                      int n = 0;
                      return dlvm::launch_chain8(batch, N, z, bias, static_cast<const float*>(x),
@@ -950,7 +961,7 @@ dlvm_status plan_rnn_backward(const dlvm_model* m, const void* params, const voi
   float* db = at<float>(dparams, static_cast<size_t>(m->offsets[1]) * 4);
   void* dz = at<void>(ws, w.dz);
   dlvm_status st = run.run(
-      elementwise_info("act_adjoint", B, H, 3.0 * double(B) * H * es), [&](hipStream_t s) {
+      [&] { return elementwise_info("act_adjoint", B, H, 3.0 * double(B) * H * es); }, [&](hipStream_t s) {
         return dlvm::launch_act_adjoint(dt, m->acts[0], B * H, seq_at(dhs, T - 1, B, H, es),
                                         seq_at(hs, T, B, H, es), seq_at(dz, T - 1, B, H, es), s);
       },
@@ -981,7 +992,7 @@ dlvm_status plan_rnn_backward(const dlvm_model* m, const void* params, const voi
   }
   if (st != DLVM_OK) return st;
   if ((st = run.gemm(du)) != DLVM_OK) return st;
-  return run.run(elementwise_info("zero_padding", 0, 1, 4.0 * m->param_count),
+  return run.run([&] { return elementwise_info("zero_padding", 0, 1, 4.0 * m->param_count); },
                  [&](hipStream_t s) {
                    return dlvm::launch_finalize(nullptr, nullptr, 0, 1.0f, nullptr, nullptr, dparams,
                                                 m->gaps, s);
@@ -1266,7 +1277,7 @@ dlvm_status enqueue_sgd(const dlvm_model* m, void* params, float* master, const 
                         float lr, hipStream_t s) {
   Launcher run(m, s, nullptr, m->n_grad_launches);
   float* mst = m->dtype == DLVM_BF16 ? master : nullptr;
-  return run.run(sgd_info(m),
+  return run.run([&] { return sgd_info(m); },
                  [&](hipStream_t st) {
                    return dlvm::launch_sgd(m->dtype, m->param_count, params, mst, dparams, lr, st);
                  },

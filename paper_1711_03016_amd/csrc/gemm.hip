@@ -2,6 +2,7 @@
 // a given problem, and the launch.
 #include <algorithm>
 #include <cstdlib>
+#include <cstring>
 
 #include "gemm_kernel.hpp"
 
@@ -57,9 +58,9 @@ int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 bool aligned16(const void* q) { return (reinterpret_cast<uintptr_t>(q) & 15u) == 0; }
 
 // The direct-to-LDS kernel moves whole 16-byte chunks: bf16 operands with
-// 16-byte aligned bases, leading dimensions and contraction extent; its
-// epilogue moves 8 consecutive outputs at a time (16-byte aligned output rows,
-// saved activation and residual).
+// 16-byte aligned bases, leading dimensions and contraction extent; the input
+// adjoint's epilogue moves 8 consecutive outputs at a time (16-byte aligned output
+// rows, saved activation and residual), the others store single values.
 bool phases_ok(const GemmDesc& d, int vw) {
   return d.A2 == nullptr || (aligned16(d.A2) && d.lda2 % vw == 0 && d.K1 % vw == 0);
 }
@@ -69,9 +70,12 @@ bool phases_ok(const GemmDesc& d, int vw) {
 // null, plans such a product as the call does.
 bool two_phase(const GemmDesc& d) { return d.A2 != nullptr || (d.K1 > 0 && d.K1 < d.K); }
 
+bool async_strides_ok(const GemmDesc& d) {
+  return d.dtype == BF16 && d.lda % 8 == 0 && d.ldb % 8 == 0 && d.K % 8 == 0 &&
+         (d.layout != Layout::NT || d.ldc % 8 == 0);
+}
 bool async_ok(const GemmDesc& d) {
-  return d.dtype == BF16 && aligned16(d.A) && aligned16(d.B) && d.lda % 8 == 0 &&
-         d.ldb % 8 == 0 && d.K % 8 == 0 && d.ldc % 8 == 0 && aligned16(d.C) &&
+  return async_strides_ok(d) && aligned16(d.A) && aligned16(d.B) && aligned16(d.C) &&
          aligned16(d.aux) && aligned16(d.residual) && aligned16(d.bias) && phases_ok(d, 8);
 }
 
@@ -164,9 +168,10 @@ double estimate_f32(const GemmDesc& d, const TileShape& t, int64_t slots, int64_
 // the bytes per cycle measured for each layout, on 64 x 256 x 356 to
 // 4096 x 1024 x 1024; times 1.5 where rows start anywhere (2049-element rows and
 // the like). The estimates of the direct-to-LDS tiles, which a product with aligned
-// rows is compared with, leave out the launch and are about 1.35 times too low where
-// the two meet (1024 x 1024 x 4096 wrt the weights in four slices on 19: 38,700
-// against 59,500 measured, 25 us on either kernel).
+// rows is compared with, leave out the launch and are too low where the two meet: wrt
+// the weights about 1.35 times (1024 x 1024 x 4096 in four slices on 19: 38,700
+// against 59,500 measured, 25 us on either kernel), the others, with at most one
+// tile per compute unit, 1.8 times (1024 x 1024 x 2048 on 12: 34,000 against 63,000).
 double estimate_wave_bf16(const GemmDesc& d, const TileShape& t, int64_t slots, int64_t kc, bool aligned) {
   static const double fix[] = {1400.0, 2000.0, 2500.0, 10000.0};
   static const double rate[4][3] = {  // NN, NT, TN
@@ -175,7 +180,8 @@ double estimate_wave_bf16(const GemmDesc& d, const TileShape& t, int64_t slots, 
   const double rounds = double(ceil_div(slots, kComputeUnits));
   const double bytes = double(t.bm + t.bn) * double(kc) * 2.0;
   const double c = rounds * (fix[i] + bytes / rate[i][static_cast<int>(d.layout)]);
-  return aligned ? c / 1.35 : 2000.0 + 1.5 * c;
+  if (!aligned) return 2000.0 + 1.5 * c;
+  return c / (d.layout == Layout::TN ? 1.35 : 1.8);
 }
 
 // Clock cycles one configuration needs: rounds of tiles over the compute
@@ -263,8 +269,7 @@ namespace {
 // ignores the operands' addresses (for sizing scratch before they exist).
 GemmPlan choose(const GemmDesc& d, bool assume_aligned, int64_t capacity, int forced,
                 int fsplits) {
-  const bool can_async = assume_aligned ? (d.dtype == BF16 && d.lda % 8 == 0 && d.ldb % 8 == 0 &&
-                                           d.K % 8 == 0 && d.ldc % 8 == 0 &&
+  const bool can_async = assume_aligned ? (async_strides_ok(d) &&
                                            (!two_phase(d) || (d.lda2 % 8 == 0 && d.K1 % 8 == 0)))
                                         : async_ok(d);
   const TileShape* best = nullptr;
@@ -282,7 +287,7 @@ GemmPlan choose(const GemmDesc& d, bool assume_aligned, int64_t capacity, int fo
     // register-staged 64 x 64 and 128 x 128 tiles are never faster (with one
     // workgroup per compute unit they cannot hide their load latency).
     if (can_async && (t.cfg == 0 || t.cfg == 1 || t.cfg == 4) && forced != t.cfg) continue;
-    if ((t.cfg == 14 || t.cfg == 15) && !xl_ok(d)) continue;
+    if ((t.cfg == 14 || t.cfg == 15) && (!xl_ok(d) || d.ldc % 8 != 0)) continue;  // (16-byte stores)
     // The direct-to-LDS tiles load one-phase products through buffer
     // descriptors: operand extents below 2^31 bytes.
     if (t.async && !two_phase(d) && !xl_ok(d)) continue;
@@ -366,6 +371,39 @@ GemmPlan choose(const GemmDesc& d, bool assume_aligned, int64_t capacity, int fo
   return pl;
 }
 
+// What choose() decided for a product of these sizes, strides, alignment and
+// options, kept per thread (a call plans ten or more products, most of them the same
+// from one call to the next; looking through the configurations took 1 to 2 us each,
+// as much as a launch). The key holds everything choose() reads; a table of fixed
+// size, the newest product of a slot replaces the one before.
+struct PlanKey {
+  int64_t v[14];
+};
+struct PlanSlot {
+  PlanKey key;
+  GemmPlan plan;
+  bool used;
+};
+constexpr int kPlanSlots = 128;
+thread_local PlanSlot t_plans[kPlanSlots];
+
+GemmPlan chosen(const GemmDesc& d, bool assume_aligned, int64_t capacity, int forced, int fsplits) {
+  const int64_t bits = static_cast<int64_t>(d.layout) | int64_t(d.dtype) << 2 | int64_t(assume_aligned) << 3 |
+                       int64_t(d.split_epilogue) << 4 | int64_t(d.chain_product) << 5 |
+                       int64_t(d.mask != nullptr) << 6 | int64_t(d.A2 != nullptr) << 7 |
+                       int64_t(!assume_aligned && async_ok(d)) << 8 | int64_t(d.splits_hint) << 16;
+  const PlanKey k{{bits, d.M, d.N, d.K, d.lda, d.ldb, d.ldc, d.lda2, d.K1, d.nvec, capacity, forced,
+                   fsplits, 0}};
+  uint64_t h = 0;
+  for (int64_t x : k.v) h = (h ^ static_cast<uint64_t>(x)) * 0x9e3779b97f4a7c15ull, h ^= h >> 29;
+  PlanSlot& slot = t_plans[h % kPlanSlots];
+  if (slot.used && std::memcmp(&slot.key, &k, sizeof k) == 0) return slot.plan;
+  slot.plan = choose(d, assume_aligned, capacity, forced, fsplits);
+  slot.key = k;
+  slot.used = true;
+  return slot.plan;
+}
+
 }  // namespace
 
 int64_t chain_partials(const GemmPlan& pl) {
@@ -374,7 +412,7 @@ int64_t chain_partials(const GemmPlan& pl) {
 }
 
 GemmPlan plan_gemm(const GemmDesc& d) {
-  return choose(d, false, d.split_ws != nullptr ? d.split_ws_elems : 0, forced_config(),
+  return chosen(d, false, d.split_ws != nullptr ? d.split_ws_elems : 0, forced_config(),
                 forced_splits());
 }
 
@@ -392,7 +430,7 @@ int64_t mask_bytes(int64_t M, int64_t N) {
 
 int64_t split_ws_elems(const GemmDesc& d) {
   if (d.layout != Layout::TN && !d.split_epilogue) return 0;
-  const GemmPlan pl = choose(d, true, int64_t(1) << 40, forced_config(), forced_splits());
+  const GemmPlan pl = chosen(d, true, int64_t(1) << 40, forced_config(), forced_splits());
   return pl.splits > 1 ? split_need(d, pl.splits) : 0;
 }
 
