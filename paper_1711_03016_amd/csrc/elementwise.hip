@@ -378,34 +378,75 @@ __global__ __launch_bounds__(kBlock) void dlvm_chain8_kernel(
 // Loss finalisation: fixed-order sum of the partials, times the seed scale
 // (skipped when out is null). Also zeroes the padding gaps of the flat
 // gradient buffer.
+//
+// One workgroup, so its time is round trips: 16 waves with four loads of each
+// array in flight per thread (4,096 partials at once; one load at a time by 256
+// threads took 16 round trips, 6.1 us for the 4,096 partials of a 16384-row loss
+// against 3.0 now), and the gaps shared out over the waves (one after the other, each
+// with its kernel-argument reads, 4.6 us for six gaps).
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(kBlock) void dlvm_finalize_kernel(const float* __restrict__ partials,
-                                                               const int32_t* __restrict__ bad,
-                                                               int n, float scale,
-                                                               float* __restrict__ out,
-                                                               int32_t* __restrict__ flags,
-                                                               float* __restrict__ zero_base,
-                                                               ZeroGaps gaps) {
-  __shared__ float red[kWaves];
-  __shared__ float redb[kWaves];
-  float v = 0.0f, nb = 0.0f;
-  for (int i = threadIdx.x; i < n; i += kBlock) {
-    v += partials[i];
-    if (bad != nullptr) nb += static_cast<float>(bad[i]);
+constexpr int kFinBlock = 1024;
+constexpr int kFinWaves = kFinBlock / 64;
+constexpr int kFinUnroll = 4;
+
+__global__ __launch_bounds__(kFinBlock) void dlvm_finalize_kernel(const float* __restrict__ partials,
+                                                                  const int32_t* __restrict__ bad,
+                                                                  int n, float scale,
+                                                                  float* __restrict__ out,
+                                                                  int32_t* __restrict__ flags,
+                                                                  float* __restrict__ zero_base,
+                                                                  ZeroGaps gaps) {
+  __shared__ float red[kFinWaves];
+  __shared__ int redb[kFinWaves];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  if (zero_base != nullptr) {
+    for (int g = wave; g < gaps.n; g += kFinWaves) {
+      const int64_t off = gaps.off[g];
+      const int len = gaps.len[g];
+      for (int i = lane; i < len; i += 64) zero_base[off + i] = 0.0f;
+    }
   }
-  const float t = block_sum(v, red);
-  const float tb = block_sum(nb, redb);
-  if (threadIdx.x == 0 && out != nullptr) {
+  if (out == nullptr) return;
+  float v = 0.0f;
+  int nb = 0;
+  for (int i0 = tid; i0 < n; i0 += kFinBlock * kFinUnroll) {
+    float x[kFinUnroll];
+    int y[kFinUnroll];
+#pragma unroll
+    for (int u = 0; u < kFinUnroll; ++u) {
+      const int i = i0 + u * kFinBlock;
+      x[u] = i < n ? partials[i] : 0.0f;
+      y[u] = bad != nullptr && i < n ? bad[i] : 0;
+    }
+#pragma unroll
+    for (int u = 0; u < kFinUnroll; ++u) {
+      v += x[u];
+      nb |= y[u];
+    }
+  }
+  v = wave_sum(v);
+#pragma unroll
+  for (int o = 32; o >= 1; o >>= 1) nb |= __shfl_xor(nb, o, 64);
+  if (lane == 0) {
+    red[wave] = v;
+    redb[wave] = nb;
+  }
+  __syncthreads();
+  if (tid == 0) {
+    float t = 0.0f;
+    int b = 0;
+#pragma unroll
+    for (int w = 0; w < kFinWaves; ++w) {
+      t += red[w];
+      b |= redb[w];
+    }
     const float loss = t * scale;
     out[0] = loss;
     if (flags != nullptr) {
-      flags[0] = tb > 0.0f ? 1 : 0;
+      flags[0] = b != 0 ? 1 : 0;
       flags[1] = isfinite(loss) ? 0 : 1;
     }
-  }
-  if (zero_base != nullptr) {
-    for (int g = 0; g < gaps.n; ++g)
-      for (int i = threadIdx.x; i < gaps.len[g]; i += kBlock) zero_base[gaps.off[g] + i] = 0.0f;
   }
 }
 
@@ -801,7 +842,7 @@ hipError_t launch_chain8(int64_t rows, int64_t cols, const float* z, const float
 hipError_t launch_finalize(const float* partials, const int32_t* bad, int n, float scale,
                            float* out, int32_t* flags, float* zero_base, const ZeroGaps& gaps,
                            hipStream_t s) {
-  launch_kernel(dlvm_finalize_kernel, dim3(1), dim3(kBlock), s, partials, bad, n, scale,
+  launch_kernel(dlvm_finalize_kernel, dim3(1), dim3(kFinBlock), s, partials, bad, n, scale,
                      out, flags, zero_base, gaps);
   return hipGetLastError();
 }

@@ -35,10 +35,11 @@
 // byte offsets inside a step that each lane computes once. They ask for the
 // alignment of one element only, so every leading dimension and size takes this
 // path. Rows past the edge of the output are read from one inside (they reach only
-// outputs that are not stored); where a load of R columns would straddle that edge,
-// and in the k-step that crosses the end of the contraction, values are loaded one
-// by one, with an offset past the descriptor's size (the hardware returns zero) for
-// what lies outside.
+// outputs that are not stored); a load of R columns that would straddle that edge
+// starts R columns before it, and its values move into place when they are multiplied.
+// In the k-step that crosses the end of the contraction (and in operands of fewer
+// than R columns) values are loaded one by one, with an offset past the descriptor's
+// size (the hardware returns zero) for what lies outside.
 #pragma once
 
 #include "common.hpp"
@@ -84,6 +85,7 @@ template <typename T, bool KMAJ, int R>
 struct WaveOffsets {
   static constexpr int E = wave_step<T>() / 4;
   uint32_t off[KMAJ ? R : E];  // byte offsets inside a step from the tile's origin
+  int ahead = 0;               // columns by which this lane's loads start early
 
   // Rows past `rows` (rows left in the operand from the tile's first) are read
   // from one inside: they only reach outputs that are not stored.
@@ -95,10 +97,12 @@ struct WaveOffsets {
         const int64_t r = 16 * i + l < rows ? 16 * i + l : 0;
         off[i] = static_cast<uint32_t>((r * ld + E * g) * static_cast<int64_t>(sizeof(T)));
       } else {
-        const int64_t r = R * l < rows ? R * l : 0;
+        const int64_t r = R * l >= rows ? 0 : R * l + R <= rows ? R * l : rows - R;
         off[i] = static_cast<uint32_t>(((E * g + i) * ld + r) * static_cast<int64_t>(sizeof(T)));
       }
     }
+    if constexpr (!KMAJ && R > 1)
+      ahead = R * l < rows && R * l + R > rows ? static_cast<int>(R * l + R - rows) : 0;
   }
   // Byte offset of value e of block i, or one outside every descriptor where
   // the row lies past `rows` or its k past `ks` (counted from the origin).
@@ -134,6 +138,29 @@ struct WaveOperand<float, KMAJ, R> : WaveOffsets<float, KMAJ, R> {
 #pragma unroll
       for (int e = 0; e < 4; ++e) buf_load<R>(f.v[e], rs, off[e]);
     }
+  }
+  // The values of loads that started early, in their places (those past the edge are
+  // anything: they reach only outputs that are not stored).
+  __device__ __forceinline__ Regs settled(const Regs& f) const {
+    Regs o;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      if constexpr (KMAJ || R == 1) {
+#pragma unroll
+        for (int i = 0; i < R; ++i) o.v[e][i] = f.v[e][i];
+      } else if constexpr (R == 2) {
+        o.v[e][0] = this->ahead ? f.v[e][1] : f.v[e][0];
+        o.v[e][1] = f.v[e][1];
+      } else {
+        const float x0 = (this->ahead & 2) ? f.v[e][2] : f.v[e][0];
+        const float x1 = (this->ahead & 2) ? f.v[e][3] : f.v[e][1];
+        o.v[e][0] = (this->ahead & 1) ? x1 : x0;
+        o.v[e][1] = (this->ahead & 1) ? f.v[e][2] : x1;
+        o.v[e][2] = (this->ahead & 1) ? f.v[e][3] : f.v[e][2];
+        o.v[e][3] = f.v[e][3];
+      }
+    }
+    return o;
   }
   // The same value by value, zeros for rows from `rows` and k from `ks` on.
   __device__ __forceinline__ void load_edge(Regs& f, const float* P, int64_t ld, int lane,
@@ -196,6 +223,23 @@ struct WaveOperand<bf16_t, KMAJ, R> : WaveOffsets<bf16_t, KMAJ, R> {
       }
     }
   }
+  __device__ __forceinline__ Regs settled(const Regs& f) const {
+    Regs o;
+#pragma unroll
+    for (int e = 0; e < (KMAJ ? R : 8); ++e) {
+      if constexpr (KMAJ) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) o.w[e][q] = f.w[e][q];
+      } else if constexpr (R == 4) {
+        const uint64_t x = ((static_cast<uint64_t>(f.w[e][1]) << 32) | f.w[e][0]) >> (16 * this->ahead);
+        o.w[e][0] = static_cast<uint32_t>(x);
+        o.w[e][1] = static_cast<uint32_t>(x >> 32);
+      } else {
+        o.w[e][0] = R == 2 ? f.w[e][0] >> (16 * this->ahead) : f.w[e][0];
+      }
+    }
+    return o;
+  }
   // The 8 values of block i.
   __device__ __forceinline__ static bf16x8 frag(const Regs& f, int i) {
     if constexpr (KMAJ) {
@@ -219,10 +263,10 @@ constexpr int wave_smem_bytes() {
 }
 
 // One output tile (`tile` from split_slice) of a product, LDS at `smem`. EDGE:
-// the tile crosses the edge of the output; EA, EB: a load of R columns of a
-// row-contiguous operand would straddle that edge, so it goes element by element.
+// the tile crosses the edge of the output; ONE: a row-contiguous operand has fewer
+// columns left than one load takes, so values are loaded one by one.
 template <typename T, typename TO, bool AK, bool BKM, int AB, int BB, int NW, int DEPTH, int EPI,
-          bool PH2, bool EDGE, bool EA, bool EB>
+          bool PH2, bool EDGE, bool ONE>
 __device__ __forceinline__ void wave_gemm_body(const Params& p, int64_t m0, int64_t n0, int tm,
                                                char* smem) {
   constexpr int TM = 16 * AB, TN = 16 * BB, LD = TN + 4;
@@ -308,18 +352,18 @@ __device__ __forceinline__ void wave_gemm_body(const Params& p, int64_t m0, int6
   auto load = [&](int d, int s) {
     int64_t ld;
     const T* pa = a_at(s, ld);
-    if constexpr (EA)
+    if constexpr (ONE)
       oa.load_edge(a[d], pa, ld, lane, p.M - m0, STEP);
     else if (PH2 && s >= nf1)
       oa2.load(a[d], pa);
     else
       oa.load(a[d], pa);
-    if constexpr (EB)
+    if constexpr (ONE)
       ob.load_edge(b[d], b_at(s), p.ldb, lane, p.N - n0, STEP);
     else
       ob.load(b[d], b_at(s));
   };
-  auto multiply = [&](const typename OA::Regs& ra, const typename OB::Regs& rb) {
+  auto products = [&](const typename OA::Regs& ra, const typename OB::Regs& rb) {
     if constexpr (sizeof(T) == 4) {
 #pragma unroll
       for (int e = 0; e < 4; ++e)
@@ -360,7 +404,14 @@ __device__ __forceinline__ void wave_gemm_body(const Params& p, int64_t m0, int6
     }
   };
 
-  // A partial step (fewer than 16 k left of a phase), its loads first of all.
+  auto multiply = [&](int d) {
+    if constexpr (EDGE && !ONE)
+      products(oa.settled(a[d]), ob.settled(b[d]));
+    else
+      products(a[d], b[d]);
+  };
+
+  // A partial step (fewer k left of a phase than a step has), its loads first of all.
   const bool t1 = PH2 && tail1 > 0 && wave == 0;
   const bool t2 = tail2 > 0 && wave == NW - 1;
   typename OA::Regs ta;
@@ -385,16 +436,16 @@ __device__ __forceinline__ void wave_gemm_body(const Params& p, int64_t m0, int6
     for (; s + DEPTH < s1; s += DEPTH) {
 #pragma unroll
       for (int d = 0; d < DEPTH; ++d) {
-        multiply(a[d], b[d]);
+        multiply(d);
         load(d, s + d + DEPTH < s1 ? s + d + DEPTH : s1 - 1);
         __builtin_amdgcn_sched_barrier(0);
       }
     }
 #pragma unroll
     for (int d = 0; d < DEPTH; ++d)
-      if (s + d < s1) multiply(a[d], b[d]);
+      if (s + d < s1) multiply(d);
   }
-  if (t1 || t2) multiply(ta, tb);
+  if (t1 || t2) products(ta, tb);
 
   // Partial tiles to LDS in row-major order. Accumulator register r of block
   // (i, j) holds the block's row 4 g + r and column l.
@@ -471,15 +522,13 @@ __device__ __forceinline__ void wave_gemm_tile(const Params& p, int tile, char* 
   const int64_t m0 = static_cast<int64_t>(tm) * (16 * AB);
   const int64_t n0 = static_cast<int64_t>(tn) * (16 * BB);
   if (m0 + 16 * AB <= p.M && n0 + 16 * BB <= p.N) {
-    wave_gemm_body<T, TO, AK, BKM, AB, BB, NW, DEPTH, EPI, PH2, false, false, false>(p, m0, n0, tm, smem);
+    wave_gemm_body<T, TO, AK, BKM, AB, BB, NW, DEPTH, EPI, PH2, false, false>(p, m0, n0, tm, smem);
   } else {
     constexpr bool CA = !AK && AB > 1, CB = !BKM && BB > 1;  // loads of several columns
-    const bool sa = CA && m0 + 16 * AB > p.M && (p.M - m0) % AB != 0;
-    const bool sb = CB && n0 + 16 * BB > p.N && (p.N - n0) % BB != 0;
-    if ((CA || CB) && (sa || sb))
-      wave_gemm_body<T, TO, AK, BKM, AB, BB, NW, DEPTH, EPI, PH2, true, CA, CB>(p, m0, n0, tm, smem);
+    if ((CA && p.M - m0 < AB) || (CB && p.N - n0 < BB))
+      wave_gemm_body<T, TO, AK, BKM, AB, BB, NW, DEPTH, EPI, PH2, true, CA || CB>(p, m0, n0, tm, smem);
     else
-      wave_gemm_body<T, TO, AK, BKM, AB, BB, NW, DEPTH, EPI, PH2, true, false, false>(p, m0, n0, tm, smem);
+      wave_gemm_body<T, TO, AK, BKM, AB, BB, NW, DEPTH, EPI, PH2, true, false>(p, m0, n0, tm, smem);
   }
 }
 

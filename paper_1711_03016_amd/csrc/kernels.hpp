@@ -210,6 +210,7 @@ struct SmallNet {
   int pwords;
   int64_t offW[kSmallMaxLayers], offB[kSmallMaxLayers];  // in dparams
   int ldw[kSmallMaxLayers];
+  uint32_t divw[kSmallMaxLayers + 1], divld[kSmallMaxLayers];  // small_div of w and ldw
   float scale;  // 1 / B
 };
 // Fill t for a network; false if it does not fit one workgroup (layers,

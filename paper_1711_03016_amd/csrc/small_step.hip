@@ -24,6 +24,14 @@
 // plain float32 fused multiply-adds: at these sizes the matrix cores would
 // not be fed.
 //
+// What bounds it is latency on one compute unit (13.1 us for the 64-32-10 network
+// before, 81K multiply-adds), so every phase waits once for whatever it can: the
+// kernel's arguments (1.2 KB; each 64-byte line a scalar load reaches for the first
+// time takes 620 cycles, and the layer loops index them) are copied to LDS by one
+// vector load beside the parameters; the sums keep 8 pairs of LDS reads in flight;
+// a phase's barrier waits for its LDS writes only, not for the gradients it stored;
+// rows and columns come from a multiplication instead of a division.
+//
 // LDS layout (words): the parameter block (W_l as [w_l][ldw_l], b_l, the
 // padding between them); H_0 .. H_L as [B][w_l]; two adjoint buffers
 // [B][maxw]; row losses, row label marks and labels [B] each.
@@ -66,19 +74,59 @@ __device__ __forceinline__ float group_sum(float v, int T) {
   return v;
 }
 
-__global__ __launch_bounds__(kSmallThreads) void dlvm_small_step_kernel(
-    SmallNet t, const float* __restrict__ params, const float* __restrict__ x,
-    const int32_t* __restrict__ labels, float* __restrict__ loss, float* __restrict__ dparams,
-    float* __restrict__ dx, int32_t* __restrict__ flags, ZeroGaps gaps) {
+// i / n for i < 2^16, n <= 2^12, with m = small_div(n).
+__device__ __forceinline__ int div_by(int i, uint32_t m) {
+  return m == 0u ? i : static_cast<int>(__umulhi(static_cast<uint32_t>(i), m));
+}
+
+// The phases exchange through LDS: wait for this wave's LDS accesses, then for the
+// other waves (global stores in flight are left alone; nothing here reads them back).
+__device__ __forceinline__ void phase_barrier() {
+  __atomic_signal_fence(__ATOMIC_SEQ_CST);
+  __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0)
+  __builtin_amdgcn_s_barrier();
+  __atomic_signal_fence(__ATOMIC_SEQ_CST);
+}
+
+struct SmallArgs {
+  SmallNet t;
+  const float* params;
+  const float* x;
+  const int32_t* labels;
+  float* loss;
+  float* dparams;
+  float* dx;
+  int32_t* flags;
+  ZeroGaps gaps;
+};
+constexpr int kArgWords = sizeof(SmallArgs) / 4;
+static_assert(sizeof(SmallArgs) % 4 == 0 && kArgWords <= kSmallThreads, "one word per thread");
+
+__global__ __launch_bounds__(kSmallThreads) void dlvm_small_step_kernel(SmallArgs args) {
   __shared__ __attribute__((aligned(16))) float sm[kSmallMaxLds / 4];
+  __shared__ __attribute__((aligned(16))) uint32_t argw[kArgWords];
   const int tid = threadIdx.x;
   const int lane = tid & 63, wave = tid >> 6;
-  const int B = t.B;
+  // the arguments as words of the kernel-argument segment (its one argument is first)
+  const uint32_t __attribute__((address_space(4)))* seg =
+      (const uint32_t __attribute__((address_space(4)))*)__builtin_amdgcn_kernarg_segment_ptr();
+  const uint32_t aw = tid < kArgWords ? seg[tid] : 0u;
+  const SmallNet& t = reinterpret_cast<const SmallArgs*>(argw)->t;  // (after the first barrier)
+  const ZeroGaps& gaps = reinterpret_cast<const SmallArgs*>(argw)->gaps;
+  const float* __restrict__ params = args.params;
+  const float* __restrict__ x = args.x;
+  const int32_t* __restrict__ labels = args.labels;
+  float* __restrict__ loss = args.loss;
+  float* __restrict__ dparams = args.dparams;
+  float* __restrict__ dx = args.dx;
+  int32_t* __restrict__ flags = args.flags;
+  const int B = args.t.B;
 
   // stage the parameter block, x and the labels (16-byte body, word tail)
   {
-    const float* pb = params + t.pbase;
-    const int np4 = t.pwords / 4, nx = B * t.w[0], nx4 = nx / 4;
+    const int pwords = args.t.pwords;
+    const float* pb = params + args.t.pbase;
+    const int np4 = pwords / 4, nx = B * args.t.w[0], nx4 = nx / 4;
     float4 pv[kStage4], xv[kStage4];
 #pragma unroll
     for (int j = 0; j < kStage4; ++j) {
@@ -87,21 +135,22 @@ __global__ __launch_bounds__(kSmallThreads) void dlvm_small_step_kernel(
       if (e < nx4) xv[j] = reinterpret_cast<const float4*>(x)[e];
     }
     const int pt = np4 * 4 + tid, xt = nx4 * 4 + tid;
-    const float ptail = pt < t.pwords ? pb[pt] : 0.0f;
+    const float ptail = pt < pwords ? pb[pt] : 0.0f;
     const float xtail = xt < nx ? x[xt] : 0.0f;
     const int lab = tid < B ? labels[tid] : 0;
-    float* xs = sm + t.hoff[0];
+    float* xs = sm + args.t.hoff[0];
+    if (tid < kArgWords) argw[tid] = aw;
 #pragma unroll
     for (int j = 0; j < kStage4; ++j) {
       const int e = tid + j * kSmallThreads;
       if (e < np4) reinterpret_cast<float4*>(sm)[e] = pv[j];
       if (e < nx4) reinterpret_cast<float4*>(xs)[e] = xv[j];
     }
-    if (pt < t.pwords) sm[pt] = ptail;
+    if (pt < pwords) sm[pt] = ptail;
     if (xt < nx) xs[xt] = xtail;
-    if (tid < B) reinterpret_cast<int*>(sm + t.labels)[tid] = lab;
+    if (tid < B) reinterpret_cast<int*>(sm + args.t.labels)[tid] = lab;
   }
-  __syncthreads();
+  phase_barrier();
 
   // forward
   for (int l = 0; l < t.L; ++l) {
@@ -111,17 +160,18 @@ __global__ __launch_bounds__(kSmallThreads) void dlvm_small_step_kernel(
     const float* bias = sm + t.boff[l];
     float* o = sm + t.hoff[l + 1];
     const bool last = l == t.L - 1;
+    const uint32_t dN = t.divw[l + 1];
     const int T = group_lanes(B * N), q = tid & (T - 1);
     for (int i = tid / T; i < B * N; i += kSmallThreads / T) {
-      const int r = i / N, n = i - r * N;
+      const int r = div_by(i, dN), n = i - r * N;
       const float* hr = h + r * K;
       float acc = 0.0f;
-#pragma unroll 4
+#pragma unroll 8
       for (int k = q; k < K; k += T) acc = fmaf(hr[k], W[k * sw + n], acc);
       acc = group_sum(acc, T) + bias[n];
       if (q == 0) o[i] = last ? acc : apply_act(act, acc);
     }
-    __syncthreads();
+    phase_barrier();
   }
 
   // softmax cross-entropy, one wave per row; the adjoint of the logits
@@ -150,7 +200,7 @@ __global__ __launch_bounds__(kSmallThreads) void dlvm_small_step_kernel(
     for (int c = lane; c < C; c += 64)
       g[r * C + c] = ps * __expf(z[c] - m) - (c == y ? t.scale : 0.0f);
   }
-  __syncthreads();
+  phase_barrier();
 
   // the mean loss and the flags (wave 0; nothing below reads what it writes)
   if (wave == 0) {
@@ -173,6 +223,7 @@ __global__ __launch_bounds__(kSmallThreads) void dlvm_small_step_kernel(
   // adjoint, last layer first
   for (int l = t.L - 1; l >= 0; --l) {
     const int K = t.w[l], N = t.w[l + 1], ld = t.ldw[l];
+    const uint32_t dld = t.divld[l], dK = t.divw[l];
     const float* W = sm + t.woff[l];
     const float* h = sm + t.hoff[l];
     float* dW = dparams + t.offW[l];
@@ -181,10 +232,10 @@ __global__ __launch_bounds__(kSmallThreads) void dlvm_small_step_kernel(
     {
       const int T = group_lanes(K * ld), q = tid & (T - 1);
       for (int i = tid / T; i < K * ld; i += kSmallThreads / T) {
-        const int k = i / ld, n = i - k * ld;
+        const int k = div_by(i, dld), n = i - k * ld;
         float acc = 0.0f;
         if (n < N) {
-#pragma unroll 4
+#pragma unroll 8
           for (int r = q; r < B; r += T) acc = fmaf(h[r * K + k], g[r * N + n], acc);
         }
         acc = group_sum(acc, T);
@@ -203,11 +254,11 @@ __global__ __launch_bounds__(kSmallThreads) void dlvm_small_step_kernel(
     if (l > 0 || t.wrt_x) {
       const int T = group_lanes(B * K), q = tid & (T - 1);
       for (int i = tid / T; i < B * K; i += kSmallThreads / T) {
-        const int r = i / K, k = i - r * K;
+        const int r = div_by(i, dK), k = i - r * K;
         const float* gr = g + r * N;
         const float* wr = W + k * ld;
         float acc = 0.0f;
-#pragma unroll 4
+#pragma unroll 8
         for (int n = q; n < N; n += T) acc = fmaf(gr[n], wr[n], acc);
         acc = group_sum(acc, T);
         if (q == 0) {
@@ -218,17 +269,23 @@ __global__ __launch_bounds__(kSmallThreads) void dlvm_small_step_kernel(
         }
       }
     }
-    __syncthreads();
+    phase_barrier();
     float* tmp = g;
     g = gn;
     gn = tmp;
   }
 
-  for (int q = 0; q < gaps.n; ++q)
-    for (int i = tid; i < gaps.len[q]; i += kSmallThreads) dparams[gaps.off[q] + i] = 0.0f;
+  for (int q = wave; q < gaps.n; q += kWaves)
+    for (int i = lane; i < gaps.len[q]; i += 64) dparams[gaps.off[q] + i] = 0.0f;
 }
 
 }  // namespace
+
+// A factor m with __umulhi(i, m) == i / n for i < 2^16, 2 <= n <= 2^12:
+// floor(2^32 / n) + 1 (its excess times i stays below 1 / n); 0 for n = 1.
+static uint32_t small_div(int n) {
+  return n == 1 ? 0u : static_cast<uint32_t>((uint64_t(1) << 32) / n + 1);
+}
 
 bool small_net(int L, const int32_t* widths, const int32_t* acts, const int64_t* offsets,
                const int64_t* ldw, int64_t B, bool wrt_x, SmallNet& t) {
@@ -278,7 +335,9 @@ bool small_net(int L, const int32_t* widths, const int32_t* acts, const int64_t*
     t.offW[l] = offsets[2 * l];
     t.offB[l] = offsets[2 * l + 1];
     t.ldw[l] = static_cast<int>(ldw[l]);
+    t.divld[l] = small_div(t.ldw[l]);
   }
+  for (int l = 0; l <= L; ++l) t.divw[l] = small_div(widths[l]);
   t.scale = static_cast<float>(1.0 / static_cast<double>(B));
   return true;
 }
@@ -287,8 +346,8 @@ hipError_t launch_small_step(const SmallNet& t, const float* params, const float
                              const int32_t* labels, float* loss, float* dparams, float* dx,
                              int32_t* flags, const ZeroGaps& gaps, hipStream_t s) {
   if (t.pwords > kSmallMaxLds / 4 || t.B * t.w[0] > kSmallMaxLds / 4) return hipErrorInvalidValue;
-  launch_kernel(dlvm_small_step_kernel, dim3(1), dim3(kSmallThreads), s, t, params, x, labels,
-                loss, dparams, dx, flags, gaps);
+  const SmallArgs a{t, params, x, labels, loss, dparams, dx, flags, gaps};
+  launch_kernel(dlvm_small_step_kernel, dim3(1), dim3(kSmallThreads), s, a);
   return hipGetLastError();
 }
 
