@@ -193,7 +193,8 @@ hipError_t launch_split_epilogue(int dtype, int out_dtype, int mode, int splits,
 // (its input, weights and activations in LDS): see small_step.hip.
 constexpr int kSmallMaxLayers = 8;
 constexpr int kSmallThreads = 1024;
-constexpr int kSmallMaxLds = 64 * 1024;                   // bytes of LDS for everything
+constexpr int kSmallMaxLds = 64 * 1024;                   // bytes of LDS for everything, rows unpadded
+constexpr int kSmallLds = 144 * 1024;                     // bytes of LDS the kernel has
 constexpr int64_t kSmallMaxMacs = int64_t(1) << 21;       // forward + both adjoints
 struct SmallNet {
   int L, B, maxw, wrt_x;
@@ -210,8 +211,9 @@ struct SmallNet {
   int pwords;
   int64_t offW[kSmallMaxLayers], offB[kSmallMaxLayers];  // in dparams
   int ldw[kSmallMaxLayers];
-  uint32_t divw[kSmallMaxLayers + 1], divld[kSmallMaxLayers];  // small_div of w and ldw
-  float scale;  // 1 / B
+  int hs[kSmallMaxLayers + 1], gs;  // row strides of H_l and of the adjoint buffers
+  uint32_t divw0;  // small_div of w[0]
+  float scale;     // 1 / B
 };
 // Fill t for a network; false if it does not fit one workgroup (layers,
 // batch, LDS) or has too much work for one compute unit.

@@ -16,25 +16,25 @@
 //             differentiated; the first layer's input adjoint is otherwise dead);
 //   finalise  the mean loss, the device flags, the padding of dparams zeroed;
 // with workgroup barriers between the phases and nothing but the results
-// written to global memory. A phase with fewer outputs than threads gives each
-// output a group of T adjacent lanes (T the largest power of two, at most 16,
-// with T x outputs <= 1024): lane q of the group sums the terms q, q + T, ...
-// and a butterfly over the group adds the T partial sums. Every sum thus runs
-// in a fixed order, so the result is the same on every run. Products are
-// plain float32 fused multiply-adds: at these sizes the matrix cores would
-// not be fed.
+// written to global memory. Every product runs on the matrix cores in 16 x 16 tiles
+// (16x16x4 float32 instructions, operands read from LDS one value per lane and
+// instruction), the tiles of a phase dealt to the waves; every sum runs in a fixed
+// order, so the result is the same on every run.
 //
-// What bounds it is latency on one compute unit (13.1 us for the 64-32-10 network
-// before, 81K multiply-adds), so every phase waits once for whatever it can: the
+// What bounds it is latency on one compute unit. With a thread per output the
+// products were bound by LDS instructions (two reads per multiply-add; the 64-32-10
+// network at batch 16 spent 5,560 cycles on its first forward product, 28,000 in all,
+// 13.1 us a launch); a matrix instruction takes two reads for 1,024 multiply-adds. The
 // kernel's arguments (1.2 KB; each 64-byte line a scalar load reaches for the first
 // time takes 620 cycles, and the layer loops index them) are copied to LDS by one
-// vector load beside the parameters; the sums keep 8 pairs of LDS reads in flight;
-// a phase's barrier waits for its LDS writes only, not for the gradients it stored;
-// rows and columns come from a multiplication instead of a division.
+// vector load beside the parameters; a phase's barrier waits for its LDS writes only,
+// not for the gradients it stored; rows of at most 16 classes stay inside 16 lanes.
 //
 // LDS layout (words): the parameter block (W_l as [w_l][ldw_l], b_l, the
-// padding between them); H_0 .. H_L as [B][w_l]; two adjoint buffers
-// [B][maxw]; row losses, row label marks and labels [B] each.
+// padding between them); H_0 .. H_L as [B][hs_l]; two adjoint buffers
+// [B][gs]; row losses, row label marks and labels [B] each. The row strides hs_l and
+// gs are the widths rounded up to 4 more than a multiple of 8 where the budget allows
+// (16 rows then lie in different banks), else the widths.
 #include "common.hpp"
 #include "kernels.hpp"
 
@@ -60,24 +60,67 @@ __device__ __forceinline__ int wave_or(int v) {
   return v;
 }
 
-// Lanes per output for a phase of `outputs` sums (uniform over the workgroup).
-__device__ __forceinline__ int group_lanes(int outputs) {
-  int t = 1;
-  while (t < 16 && 2 * t * outputs <= kSmallThreads) t *= 2;
-  return t;
+// Sum and maximum over the 16 lanes of a row (every lane ends with the same bits).
+template <int CTRL>
+__device__ __forceinline__ float row_rot(float v) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, 0xf, 0xf, true));
+}
+__device__ __forceinline__ float row16_sum(float v) {
+  v += row_rot<0x128>(v);  // rotations by 8, 4, 2, 1 lanes
+  v += row_rot<0x124>(v);
+  v += row_rot<0x122>(v);
+  return v + row_rot<0x121>(v);
+}
+__device__ __forceinline__ float row16_max(float v) {
+  v = fmaxf(v, row_rot<0x128>(v));
+  v = fmaxf(v, row_rot<0x124>(v));
+  v = fmaxf(v, row_rot<0x122>(v));
+  return fmaxf(v, row_rot<0x121>(v));
 }
 
-// Sum of v over the T adjacent lanes of a group (T a power of two <= 16;
-// every lane of the group active).
-__device__ __forceinline__ float group_sum(float v, int T) {
-  for (int o = T >> 1; o > 0; o >>= 1) v += __shfl_xor(v, o);
-  return v;
+// One 16 x 16 tile of a product over K terms from LDS: A(m, k) at a[m * am + k * ak]
+// for the tile's rows m < M (rows past it are read from row 0 and give outputs that
+// are not stored), B(k, n) at b[n * bn + k * bk] for n < N. Lane 16 g + l of an
+// instruction holds row (column) l at the g-th of its 4 k; the result's register r
+// holds row 4 g + r, column l. Two accumulators take the instructions in turn.
+__device__ __forceinline__ f32x4 lds_tile(const float* __restrict__ a, int am, int ak, int M,
+                                          const float* __restrict__ b, int bn, int bk, int N, int K,
+                                          int lane) {
+  const int l = lane & 15, g = lane >> 4;
+  const float* pa = a + (l < M ? l * am : 0) + g * ak;
+  const float* pb = b + (l < N ? l * bn : 0) + g * bk;
+  f32x4 c0 = {0.0f, 0.0f, 0.0f, 0.0f}, c1 = c0;
+  const int full = K >> 2;
+  int s = 0;
+  for (; s + 4 <= full; s += 4) {
+    float x[4], y[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      x[u] = pa[4 * u * ak];
+      y[u] = pb[4 * u * bk];
+    }
+    pa += 16 * ak;
+    pb += 16 * bk;
+    c0 = __builtin_amdgcn_mfma_f32_16x16x4f32(x[0], y[0], c0, 0, 0, 0);
+    c1 = __builtin_amdgcn_mfma_f32_16x16x4f32(x[1], y[1], c1, 0, 0, 0);
+    c0 = __builtin_amdgcn_mfma_f32_16x16x4f32(x[2], y[2], c0, 0, 0, 0);
+    c1 = __builtin_amdgcn_mfma_f32_16x16x4f32(x[3], y[3], c1, 0, 0, 0);
+  }
+  for (; 4 * s < K; ++s) {  // (the last one may hold fewer than 4 k)
+    const bool in = 4 * s + g < K;
+    const float x = in ? *pa : 0.0f, y = in ? *pb : 0.0f;
+    pa += 4 * ak;
+    pb += 4 * bk;
+    c0 = __builtin_amdgcn_mfma_f32_16x16x4f32(x, y, c0, 0, 0, 0);
+  }
+  return c0 + c1;
 }
 
 // i / n for i < 2^16, n <= 2^12, with m = small_div(n).
 __device__ __forceinline__ int div_by(int i, uint32_t m) {
   return m == 0u ? i : static_cast<int>(__umulhi(static_cast<uint32_t>(i), m));
 }
+__device__ __forceinline__ int tiles16(int n) { return (n + 15) >> 4; }
 
 // The phases exchange through LDS: wait for this wave's LDS accesses, then for the
 // other waves (global stores in flight are left alone; nothing here reads them back).
@@ -103,10 +146,11 @@ constexpr int kArgWords = sizeof(SmallArgs) / 4;
 static_assert(sizeof(SmallArgs) % 4 == 0 && kArgWords <= kSmallThreads, "one word per thread");
 
 __global__ __launch_bounds__(kSmallThreads) void dlvm_small_step_kernel(SmallArgs args) {
-  __shared__ __attribute__((aligned(16))) float sm[kSmallMaxLds / 4];
+  __shared__ __attribute__((aligned(16))) float sm[kSmallLds / 4];
   __shared__ __attribute__((aligned(16))) uint32_t argw[kArgWords];
   const int tid = threadIdx.x;
-  const int lane = tid & 63, wave = tid >> 6;
+  const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int l16 = lane & 15, g16 = lane >> 4;
   // the arguments as words of the kernel-argument segment (its one argument is first)
   const uint32_t __attribute__((address_space(4)))* seg =
       (const uint32_t __attribute__((address_space(4)))*)__builtin_amdgcn_kernarg_segment_ptr();
@@ -126,7 +170,9 @@ __global__ __launch_bounds__(kSmallThreads) void dlvm_small_step_kernel(SmallArg
   {
     const int pwords = args.t.pwords;
     const float* pb = params + args.t.pbase;
-    const int np4 = pwords / 4, nx = B * args.t.w[0], nx4 = nx / 4;
+    const int w0 = args.t.w[0], xs_ld = args.t.hs[0];
+    const uint32_t dx0 = args.t.divw0;
+    const int np4 = pwords / 4, nx = B * w0, nx4 = nx / 4;
     float4 pv[kStage4], xv[kStage4];
 #pragma unroll
     for (int j = 0; j < kStage4; ++j) {
@@ -144,10 +190,20 @@ __global__ __launch_bounds__(kSmallThreads) void dlvm_small_step_kernel(SmallArg
     for (int j = 0; j < kStage4; ++j) {
       const int e = tid + j * kSmallThreads;
       if (e < np4) reinterpret_cast<float4*>(sm)[e] = pv[j];
-      if (e < nx4) reinterpret_cast<float4*>(xs)[e] = xv[j];
+      if (e < nx4) {
+        const float v[4] = {xv[j].x, xv[j].y, xv[j].z, xv[j].w};
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const int i = 4 * e + q, r = div_by(i, dx0);
+          xs[r * xs_ld + i - r * w0] = v[q];
+        }
+      }
     }
     if (pt < pwords) sm[pt] = ptail;
-    if (xt < nx) xs[xt] = xtail;
+    if (xt < nx) {
+      const int r = div_by(xt, dx0);
+      xs[r * xs_ld + xt - r * w0] = xtail;
+    }
     if (tid < B) reinterpret_cast<int*>(sm + args.t.labels)[tid] = lab;
   }
   phase_barrier();
@@ -155,55 +211,81 @@ __global__ __launch_bounds__(kSmallThreads) void dlvm_small_step_kernel(SmallArg
   // forward
   for (int l = 0; l < t.L; ++l) {
     const int K = t.w[l], N = t.w[l + 1], sw = t.ldw[l], act = t.act[l];
+    const int hi = t.hs[l], ho = t.hs[l + 1];
     const float* h = sm + t.hoff[l];
     const float* W = sm + t.woff[l];
     const float* bias = sm + t.boff[l];
     float* o = sm + t.hoff[l + 1];
     const bool last = l == t.L - 1;
-    const uint32_t dN = t.divw[l + 1];
-    const int T = group_lanes(B * N), q = tid & (T - 1);
-    for (int i = tid / T; i < B * N; i += kSmallThreads / T) {
-      const int r = div_by(i, dN), n = i - r * N;
-      const float* hr = h + r * K;
-      float acc = 0.0f;
-#pragma unroll 8
-      for (int k = q; k < K; k += T) acc = fmaf(hr[k], W[k * sw + n], acc);
-      acc = group_sum(acc, T) + bias[n];
-      if (q == 0) o[i] = last ? acc : apply_act(act, acc);
+    const int tn = tiles16(N), nt = tiles16(B) * tn;
+    for (int q = wave; q < nt; q += kWaves) {
+      const int m0 = q / tn * 16, n0 = q % tn * 16;
+      const f32x4 c = lds_tile(h + m0 * hi, hi, 1, B - m0, W + n0, 1, sw, N - n0, K, lane);
+      const int n = n0 + l16;
+      if (n < N) {
+        const float bv = bias[n];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const int row = m0 + 4 * g16 + r;
+          const float v = c[r] + bv;
+          if (row < B) o[row * ho + n] = last ? v : apply_act(act, v);
+        }
+      }
     }
     phase_barrier();
   }
 
-  // softmax cross-entropy, one wave per row; the adjoint of the logits
-  const int C = t.w[t.L];
+  // softmax cross-entropy and the adjoint of the logits: at most 16 classes, one row
+  // per 16 lanes; else one row per wave
+  const int C = t.w[t.L], zs = t.hs[t.L], gs = t.gs;
   const float* Z = sm + t.hoff[t.L];
   float* rowloss = sm + t.rowloss;
   int* rowbad = reinterpret_cast<int*>(sm + t.rowbad);
   const int* lab = reinterpret_cast<const int*>(sm + t.labels);
   float* g = sm + t.g0;
   float* gn = sm + t.g1;
-  for (int r = wave; r < B; r += kWaves) {
-    const float* z = Z + r * C;
-    float m = -INFINITY;
-    for (int c = lane; c < C; c += 64) m = fmaxf(m, z[c]);
-    m = wave_max(m);
-    float s = 0.0f;
-    for (int c = lane; c < C; c += 64) s += __expf(z[c] - m);
-    s = wave_sum(s);
-    const int y = lab[r];
-    const bool ok = y >= 0 && y < C;
-    if (lane == 0) {
-      rowbad[r] = ok ? 0 : 1;
-      rowloss[r] = ok ? (m + __logf(s)) - z[y] : NAN;
+  if (C <= 16) {
+    for (int r0 = wave * 4; r0 < B; r0 += kWaves * 4) {
+      const int r = r0 + g16, rr = r < B ? r : 0;
+      const float z = l16 < C ? Z[rr * zs + l16] : -INFINITY;
+      const int y = lab[rr];
+      const bool ok = y >= 0 && y < C;
+      const float m = row16_max(z);
+      const float e = l16 < C ? __expf(z - m) : 0.0f;
+      const float s = row16_sum(e);
+      if (r < B) {
+        if (l16 == 0) {
+          rowbad[r] = ok ? 0 : 1;
+          rowloss[r] = ok ? (m + __logf(s)) - Z[r * zs + y] : NAN;
+        }
+        if (l16 < C) g[r * gs + l16] = t.scale / s * e - (l16 == y ? t.scale : 0.0f);
+      }
     }
-    const float ps = t.scale / s;
-    for (int c = lane; c < C; c += 64)
-      g[r * C + c] = ps * __expf(z[c] - m) - (c == y ? t.scale : 0.0f);
+  } else {
+    for (int r = wave; r < B; r += kWaves) {
+      const float* z = Z + r * zs;
+      float m = -INFINITY;
+      for (int c = lane; c < C; c += 64) m = fmaxf(m, z[c]);
+      m = wave_max(m);
+      float s = 0.0f;
+      for (int c = lane; c < C; c += 64) s += __expf(z[c] - m);
+      s = wave_sum(s);
+      const int y = lab[r];
+      const bool ok = y >= 0 && y < C;
+      if (lane == 0) {
+        rowbad[r] = ok ? 0 : 1;
+        rowloss[r] = ok ? (m + __logf(s)) - z[y] : NAN;
+      }
+      const float ps = t.scale / s;
+      for (int c = lane; c < C; c += 64)
+        g[r * gs + c] = ps * __expf(z[c] - m) - (c == y ? t.scale : 0.0f);
+    }
   }
   phase_barrier();
 
-  // the mean loss and the flags (wave 0; nothing below reads what it writes)
-  if (wave == 0) {
+  // the mean loss and the flags (the last wave, which gets the fewest tiles below;
+  // nothing reads what it writes)
+  if (wave == kWaves - 1) {
     float s = 0.0f;
     int bad = 0;
     for (int r = lane; r < B; r += 64) {
@@ -220,53 +302,51 @@ __global__ __launch_bounds__(kSmallThreads) void dlvm_small_step_kernel(SmallArg
     }
   }
 
-  // adjoint, last layer first
+  // adjoint, last layer first: the tiles of dZ_{l-1} (or dx), then of dW, then the
+  // column sums
   for (int l = t.L - 1; l >= 0; --l) {
-    const int K = t.w[l], N = t.w[l + 1], ld = t.ldw[l];
-    const uint32_t dld = t.divld[l], dK = t.divw[l];
+    const int K = t.w[l], N = t.w[l + 1], ld = t.ldw[l], hi = t.hs[l];
     const float* W = sm + t.woff[l];
     const float* h = sm + t.hoff[l];
     float* dW = dparams + t.offW[l];
     float* db = dparams + t.offB[l];
-    // dW [K, ld] (padding columns zero) and db [N]
-    {
-      const int T = group_lanes(K * ld), q = tid & (T - 1);
-      for (int i = tid / T; i < K * ld; i += kSmallThreads / T) {
-        const int k = div_by(i, dld), n = i - k * ld;
-        float acc = 0.0f;
-        if (n < N) {
-#pragma unroll 8
-          for (int r = q; r < B; r += T) acc = fmaf(h[r * K + k], g[r * N + n], acc);
+    const int tk = tiles16(K), tl = tiles16(ld);
+    const int nx = l > 0 || t.wrt_x ? tiles16(B) * tk : 0;
+    const int nw = tk * tl, nb = tiles16(N);
+    for (int q = wave; q < nx + nw + nb; q += kWaves) {
+      if (q < nx) {
+        const int m0 = q / tk * 16, k0 = q % tk * 16;
+        const f32x4 c = lds_tile(g + m0 * gs, gs, 1, B - m0, W + k0 * ld, ld, 1, K - k0, N, lane);
+        const int k = k0 + l16;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const int row = m0 + 4 * g16 + r;
+          if (k < K && row < B) {
+            if (l > 0)
+              gn[row * gs + k] = c[r] * act_grad_from_output(t.act[l - 1], h[row * hi + k]);
+            else
+              dx[row * K + k] = c[r];
+          }
         }
-        acc = group_sum(acc, T);
-        if (q == 0) dW[i] = acc;
-      }
-    }
-    {
-      const int T = group_lanes(N), q = tid & (T - 1);
-      for (int n = tid / T; n < N; n += kSmallThreads / T) {
-        float acc = 0.0f;
-        for (int r = q; r < B; r += T) acc += g[r * N + n];
-        acc = group_sum(acc, T);
-        if (q == 0) db[n] = acc;
-      }
-    }
-    if (l > 0 || t.wrt_x) {
-      const int T = group_lanes(B * K), q = tid & (T - 1);
-      for (int i = tid / T; i < B * K; i += kSmallThreads / T) {
-        const int r = div_by(i, dK), k = i - r * K;
-        const float* gr = g + r * N;
-        const float* wr = W + k * ld;
-        float acc = 0.0f;
-#pragma unroll 8
-        for (int n = q; n < N; n += T) acc = fmaf(gr[n], wr[n], acc);
-        acc = group_sum(acc, T);
-        if (q == 0) {
-          if (l > 0)
-            gn[i] = acc * act_grad_from_output(t.act[l - 1], h[i]);
-          else
-            dx[i] = acc;
+      } else if (q < nx + nw) {
+        // dW [K, ld] (padding columns zero)
+        const int i = q - nx, k0 = i / tl * 16, n0 = i % tl * 16;
+        const f32x4 c = lds_tile(h + k0, 1, hi, K - k0, g + n0, 1, gs, N - n0, B, lane);
+        const int n = n0 + l16;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const int k = k0 + 4 * g16 + r;
+          if (k < K && n < ld) dW[k * ld + n] = n < N ? c[r] : 0.0f;
         }
+      } else {
+        // db [N]: 16 columns per wave, every fourth row per lane group
+        const int n = (q - nx - nw) * 16 + l16;
+        float s = 0.0f;
+        if (n < N)
+          for (int r = g16; r < B; r += 4) s += g[r * gs + n];
+        s += __shfl_xor(s, 16, 64);
+        s += __shfl_xor(s, 32, 64);
+        if (g16 == 0 && n < N) db[n] = s;
       }
     }
     phase_barrier();
@@ -312,14 +392,32 @@ bool small_net(int L, const int32_t* widths, const int32_t* acts, const int64_t*
   take(pwords);
   int64_t hoff[kSmallMaxLayers + 1];
   for (int l = 0; l <= L; ++l) hoff[l] = take(B * widths[l]);
-  const int64_t g0 = take(B * t.maxw), g1 = take(B * t.maxw);
-  const int64_t rl = take(B), rb = take(B), lb = take(B);
+  int64_t g0 = take(B * t.maxw), g1 = take(B * t.maxw);
+  int64_t rl = take(B), rb = take(B), lb = take(B);
   int64_t macs = 0;
   for (int l = 0; l < L; ++l) {
     if (ldw[l] > 4096) return false;
     macs += 3 * B * int64_t(widths[l]) * widths[l + 1];
   }
   if (words > kSmallMaxLds / 4 || macs > kSmallMaxMacs) return false;
+  // the rows apart (see the layout above) where that fits the workgroup's LDS
+  auto apart = [](int w) { return (w + 3) / 8 * 8 + 4; };
+  static_assert(kSmallLds >= kSmallMaxLds, "unpadded rows always fit");
+  for (int pad = 1; pad >= 0; --pad) {
+    t.gs = pad ? apart(t.maxw) : t.maxw;
+    words = 0;
+    take(pwords);
+    for (int l = 0; l <= L; ++l) {
+      t.hs[l] = pad ? apart(widths[l]) : widths[l];
+      hoff[l] = take(B * t.hs[l]);
+    }
+    g0 = take(B * t.gs);
+    g1 = take(B * t.gs);
+    rl = take(B);
+    rb = take(B);
+    lb = take(B);
+    if (words <= kSmallLds / 4) break;
+  }
   t.pbase = pbase;
   t.pwords = static_cast<int>(pwords);
   for (int l = 0; l <= L; ++l) t.hoff[l] = static_cast<int>(hoff[l]);
@@ -335,9 +433,8 @@ bool small_net(int L, const int32_t* widths, const int32_t* acts, const int64_t*
     t.offW[l] = offsets[2 * l];
     t.offB[l] = offsets[2 * l + 1];
     t.ldw[l] = static_cast<int>(ldw[l]);
-    t.divld[l] = small_div(t.ldw[l]);
   }
-  for (int l = 0; l <= L; ++l) t.divw[l] = small_div(widths[l]);
+  t.divw0 = small_div(widths[0]);
   t.scale = static_cast<float>(1.0 / static_cast<double>(B));
   return true;
 }
