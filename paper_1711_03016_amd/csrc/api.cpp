@@ -146,9 +146,9 @@ WsLayout ws_layout(const dlvm_model* m, int64_t B) {
   off = align_up(off + 16);
   int64_t np = std::max<int64_t>(dlvm::softmax_xent_partials(B),
                                  dlvm::chain8_partials(B, m->widths[m->L]));
-  // the chain epilogue writes one partial per wavefront; every register-staged
-  // configuration gives each wavefront at least a 32 x 32 block
-  if (m->chain_epi) np = std::max<int64_t>(np, (B + 31) / 32 * ((m->widths[m->L] + 31) / 32));
+  // the chain epilogue writes one partial per wavefront of at least a 32 x 32 block,
+  // or one per tile of at least 16 x 16
+  if (m->chain_epi) np = std::max<int64_t>(np, (B + 15) / 16 * ((m->widths[m->L] + 15) / 16));
   w.partials = off;
   off = align_up(off + static_cast<size_t>(np) * 4);
   w.bad = off;
@@ -193,6 +193,7 @@ WsLayout ws_layout(const dlvm_model* m, int64_t B) {
     GemmDesc d = gemm_nn(m->dtype, m->dtype, m->acts[l], B, m->widths[l + 1], m->widths[l], 1.0f,
                          nullptr, nullptr, m->ldw[l], nullptr, nullptr, m->widths[l + 1]);
     d.split_epilogue = true;
+    d.sum_order = m->dtype == DLVM_F32 && m->acts[l] == DLVM_ACT_RELU;
     w.splitk_elems = std::max<int64_t>(w.splitk_elems, dlvm::split_ws_elems(d));
   }
   const int hs = head_splits(m, B);
@@ -465,6 +466,7 @@ GemmDesc hidden_desc(const dlvm_model* m, const void* params, const void* in, in
                        param_ptr(m, params, m->offsets[2 * l]), m->ldw[l],
                        param_ptr(m, params, m->offsets[2 * l + 1]), out, m->widths[l + 1]);
   d.split_epilogue = true;
+  d.sum_order = dt == DLVM_F32 && m->acts[l] == DLVM_ACT_RELU;
   d.split_ws = split_ws;
   d.split_ws_elems = split_elems;
   return d;
@@ -662,7 +664,7 @@ dlvm_status plan_gradient(const dlvm_model* m, const void* params, const void* x
       // workspace, xbar into dx, one loss partial per wavefront.
       GemmDesc d = gemm_nn(dt, DLVM_F32, DLVM_ACT_NONE, batch, N, K, 1.0f, x, P(0), N, P(1), zbar, N);
       d.aux = x;
-      d.chain_epilogue = d.chain_product = true;
+      d.chain_epilogue = true;
       d.C2 = dx;
       d.partials = partials;
       d.inv_n = scale;
@@ -678,9 +680,9 @@ dlvm_status plan_gradient(const dlvm_model* m, const void* params, const void* x
           [&](hipStream_t s) { return dlvm::launch_gemm(d, pl, s); },
                    "chain product launch");
     } else {
-      GemmDesc zd = gemm_nn(dt, DLVM_F32, DLVM_ACT_NONE, batch, N, K, 1.0f, x, P(0), N, nullptr, z, N);
-      zd.chain_product = true;
-      if ((st = run.gemm(zd)) != DLVM_OK) return st;
+      if ((st = run.gemm(gemm_nn(dt, DLVM_F32, DLVM_ACT_NONE, batch, N, K, 1.0f, x, P(0), N,
+                                 nullptr, z, N))) != DLVM_OK)
+        return st;
       np = dlvm::chain8_partials(batch, N);
       st = run.run([&] { return elementwise_info("chain8", batch, N, 16.0 * double(batch) * N + 4.0 * N); },
                    [&](hipStream_t s) {
@@ -716,7 +718,28 @@ dlvm_status plan_gradient(const dlvm_model* m, const void* params, const void* x
                           P(2 * (L - 1)), m->ldw[L - 1], P(2 * L - 1), at<void>(ws, w.logits), C);
   head.split_ws = at<float>(ws, w.splitk);
   head.split_ws_elems = w.splitk_elems;
-  head.splits_hint = head_splits(m, batch);
+  const int hs = head_splits(m, batch);
+  void* const dzL = at<void>(ws, w.dz[L - 1]);
+  if (dlvm::head_xent_ok(head, ldc)) {
+    // (few classes: product and loss share a launch, whose waves split the
+    // contraction; the logits are stored where dlvm_workspace_tensor promises them)
+    if (hs > 1) head.C = nullptr;
+    st = run.run(
+        [&] {
+          LaunchInfo info = gemm_info(head);
+          info.name = hs > 1 ? std::string("split_softmax_xent") : info.name + "_softmax_xent";
+          info.bytes += double(batch) * C * ((hs > 1 ? -4.0 : 0.0) + es) + 4.0 * batch;
+          return info;
+        },
+        [&](hipStream_t s) {
+          return dlvm::launch_head_xent(head, labels, scale, dzL, ldc, partials, bad, &np, s);
+        },
+        "output layer and loss launch");
+    if (st != DLVM_OK) return st;
+    if ((st = finalize()) != DLVM_OK) return st;
+    return plan_adjoint_layers(m, params, x, batch, dparams, dx, ws, w, run);
+  }
+  head.splits_hint = hs;
   dlvm::GemmPlan hp{};
   if ((st = run.gemm_raw(head, hp)) != DLVM_OK) return st;
   if (hp.splits > 1) {

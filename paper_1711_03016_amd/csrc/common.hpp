@@ -79,6 +79,25 @@ __device__ __forceinline__ float act_grad_from_output(int act, float h) {
   }
 }
 
+// Sum and maximum over the 16 lanes of a row (every lane ends with the same bits):
+// rotations by 8, 4, 2 and 1 lanes inside the row.
+template <int CTRL>
+__device__ __forceinline__ float row_rot(float v) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, 0xf, 0xf, true));
+}
+__device__ __forceinline__ float row16_sum(float v) {
+  v += row_rot<0x128>(v);
+  v += row_rot<0x124>(v);
+  v += row_rot<0x122>(v);
+  return v + row_rot<0x121>(v);
+}
+__device__ __forceinline__ float row16_max(float v) {
+  v = fmaxf(v, row_rot<0x128>(v));
+  v = fmaxf(v, row_rot<0x124>(v));
+  v = fmaxf(v, row_rot<0x122>(v));
+  return fmaxf(v, row_rot<0x121>(v));
+}
+
 // One element of the eight-operator chain and its adjoint: a = tanh(z + b),
 // s = sigmoid(0.5 a + 1), e = s x; returns e^2 (the loss term before the
 // mean); with the seed 1 / n of the mean, zbar = dL/dz and xbar = dL/dx (the

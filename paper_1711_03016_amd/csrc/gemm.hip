@@ -22,8 +22,9 @@ constexpr double kL2BytesPerClock = 64.0;
 // Configurations 0-5 are the register-staged kernel (gemm_kernel.hpp), 10-13, 16
 // and 17 the bf16 kernel with direct-to-LDS loads (gemm_async.hpp; 18 and 19 with
 // two k-groups of waves), 14-15 the four-wave bf16 kernel (gemm_xl.hpp). Float32
-// products run on 6-9 (gemm_wave.hpp) and 20-22 (gemm_f32.hpp); 3 is left to them
-// for leading dimensions whose byte offsets those cannot hold.
+// products run on 6-9 (gemm_wave.hpp) and 20-22 (gemm_f32.hpp); 0-4 are left to
+// the forward products that keep their order of sums (GemmDesc::sum_order), and 3
+// to leading dimensions whose byte offsets the others cannot hold.
 struct TileShape {
   int cfg;
   int bm, bn;
@@ -120,7 +121,7 @@ bool xl_phases_ok(const GemmDesc& d) {
 bool wave_config(int cfg) { return cfg >= 6 && cfg <= 9; }
 bool wave_ok(const GemmDesc& d) {
   const int64_t lim = int64_t(1) << 22;
-  return !d.chain_product && d.mask == nullptr && d.lda <= lim && d.ldb <= lim &&
+  return !d.sum_order && d.mask == nullptr && d.lda <= lim && d.ldb <= lim &&
          (!two_phase(d) || d.lda2 <= lim);
 }
 
@@ -129,7 +130,8 @@ bool wave_ok(const GemmDesc& d) {
 bool f32_config(int cfg) { return cfg >= 20 && cfg <= 22; }
 bool f32_ok(const GemmDesc& d) {
   const int64_t lim = int64_t(1) << 20;
-  return d.dtype == F32 && d.lda <= lim && d.ldb <= lim && (!two_phase(d) || d.lda2 <= lim);
+  return !d.sum_order && d.dtype == F32 && d.lda <= lim && d.ldb <= lim &&
+         (!two_phase(d) || d.lda2 <= lim);
 }
 
 // k per slice when K is split `splits` ways (a multiple of 64, so every
@@ -193,7 +195,13 @@ double estimate(const GemmDesc& d, const TileShape& t, int splits, bool aligned)
   const int64_t kc = splits > 1 ? slice_k(d.K, splits) : d.K;
   const int64_t slices = ceil_div(d.K, kc);
   double c;
-  if (d.dtype == F32) {
+  if (d.sum_order) {
+    // (the register-staged tiles, shares of the matrix rate measured on large products)
+    static const double eff[] = {0.8, 0.6, 0.6, 0.5, 0.65, 0.5};
+    const double flops = 2.0 * t.bm * t.bn * double(kc) / (kRateF32 * eff[t.cfg]);
+    const double bytes = double(t.bm + t.bn) * double(kc) * 4.0 / kL2BytesPerClock;
+    c = double(ceil_div(tiles * slices, kComputeUnits)) * (std::max(flops, bytes) + kTileFixed);
+  } else if (d.dtype == F32) {
     c = estimate_f32(d, t, tiles * slices, kc);
   } else if (wave_config(t.cfg)) {
     c = estimate_wave_bf16(d, t, tiles * slices, kc, aligned);
@@ -283,7 +291,9 @@ GemmPlan choose(const GemmDesc& d, bool assume_aligned, int64_t capacity, int fo
     if (t.cfg == 5 && forced != 5) continue;
     if (wave_config(t.cfg) && !wave_ok(d)) continue;
     if (f32_config(t.cfg) && !f32_ok(d)) continue;
-    if (d.dtype == F32 && !wave_config(t.cfg) && !f32_config(t.cfg) && (t.cfg != 3 || f32_ok(d))) continue;
+    if (d.dtype == F32 && !d.sum_order && !wave_config(t.cfg) && !f32_config(t.cfg) &&
+        (t.cfg != 3 || f32_ok(d)))
+      continue;
     if (t.async && !can_async) continue;
     if (t.async && d.dtype == F32) continue;
     // Measured: where the direct-to-LDS kernels can run a bf16 product, the
@@ -392,8 +402,8 @@ thread_local PlanSlot t_plans[kPlanSlots];
 
 GemmPlan chosen(const GemmDesc& d, bool assume_aligned, int64_t capacity, int forced, int fsplits) {
   const int64_t bits = static_cast<int64_t>(d.layout) | int64_t(d.dtype) << 2 | int64_t(assume_aligned) << 3 |
-                       int64_t(d.split_epilogue) << 4 | int64_t(d.chain_product) << 5 |
-                       int64_t(d.mask != nullptr) << 6 | int64_t(d.A2 != nullptr) << 7 |
+                       int64_t(d.split_epilogue) << 4 |
+                       int64_t(d.sum_order) << 9 | int64_t(d.mask != nullptr) << 6 | int64_t(d.A2 != nullptr) << 7 |
                        int64_t(!assume_aligned && async_ok(d)) << 8 | int64_t(d.splits_hint) << 16;
   const PlanKey k{{bits, d.M, d.N, d.K, d.lda, d.ldb, d.ldc, d.lda2, d.K1, d.nvec, capacity, forced,
                    fsplits, 0}};
@@ -410,7 +420,7 @@ GemmPlan chosen(const GemmDesc& d, bool assume_aligned, int64_t capacity, int fo
 }  // namespace
 
 int64_t chain_partials(const GemmPlan& pl) {
-  const int waves = 4;  // (configurations 20-22: 2 x 2)
+  const int waves = wave_config(pl.cfg) ? 1 : 4;  // (configurations 20-22: 2 x 2 waves)
   return static_cast<int64_t>(pl.tiles_m) * pl.tiles_n * waves;
 }
 
@@ -542,6 +552,33 @@ hipError_t launch_gemm(const GemmDesc& d, const GemmPlan& pl, hipStream_t s) {
     case Layout::TN: return gemm::launch_tn(p, d.dtype, pl.cfg, grid, va, vb, s);
   }
   return hipErrorInvalidValue;
+}
+
+bool head_xent_ok(const GemmDesc& head, int64_t ld_dlogits) {
+  return head.layout == Layout::NN && head.N <= 32 && ld_dlogits <= (head.N <= 16 ? 16 : 32) && wave_ok(head);
+}
+
+hipError_t launch_head_xent(const GemmDesc& head, const int32_t* labels, float scale, void* dlogits,
+                            int64_t ld_dlogits, float* partials, int32_t* bad, int* n_partials,
+                            hipStream_t s) {
+  if (!head_xent_ok(head, ld_dlogits)) return hipErrorInvalidValue;
+  GemmPlan pl{};
+  pl.cfg = head.N <= 16 ? 6 : 7;
+  pl.bm = 16;
+  pl.bn = head.N <= 16 ? 16 : 32;
+  pl.tiles_m = static_cast<int>(ceil_div(head.M, 16));
+  pl.tiles_n = 1;
+  pl.splits = 1;
+  pl.k_chunk = head.K;
+  gemm::Params p = make_params(head, pl);
+  p.aux = labels;
+  p.C2 = dlogits;
+  p.lda2 = ld_dlogits;
+  p.inv_n = scale;
+  p.partials = partials;
+  p.residual = bad;
+  *n_partials = pl.tiles_m;
+  return gemm::launch_wave_xent(p, head.dtype, s);
 }
 
 bool pairable(const GemmDesc& tn, const GemmPlan& ptn, const GemmDesc& nt, const GemmPlan& pnt) {

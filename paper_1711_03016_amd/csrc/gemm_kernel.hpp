@@ -52,7 +52,7 @@ namespace gemm {
 constexpr int kRowStride = 144;  // bytes per LDS row: 128 bytes of k plus 16 of padding
 constexpr int kChunks = 8;       // 16-byte chunks of k per LDS row
 
-enum Epi { EPI_STORE = 0, EPI_DACT = 1, EPI_DW = 2, EPI_CHAIN = 3 };
+enum Epi { EPI_STORE = 0, EPI_DACT = 1, EPI_DW = 2, EPI_CHAIN = 3, EPI_XENT = 4 };
 
 template <typename T> struct Elem;
 template <> struct Elem<float> { static constexpr int VW = 4; static constexpr int BK = 32; };
@@ -88,7 +88,13 @@ struct Params {
   int res_pre;  // EPI_DACT: (acc + R) * act'(Hprev) instead of acc * act'(Hprev) + R
   // EPI_CHAIN (float32 NN): the eight-operator chain on z = acc with bias[n]
   // and x_skip = aux (same shape as C): C receives zbar, C2 xbar, and each
-  // wavefront of tile t writes its sum of e^2 to partials[t * WM * WN + wave].
+  // wavefront of tile t writes its sum of e^2 to partials[t * WM * WN + wave] (the
+  // waves that share a contraction: one sum per tile t).
+  // EPI_XENT (NN, tiles as wide as the output): softmax cross-entropy of the rows of
+  // act-free logits acc + bias: labels in aux, dlogits (storage type, row stride lda2,
+  // columns from N on zero) to C2, seed scale inv_n, each tile's sum of row losses to
+  // partials[t] and its count of labels out of range to `residual` (int32, by tile);
+  // the logits themselves to C unless it is null.
   void* C2;
   float* partials;
   float inv_n;
@@ -775,6 +781,8 @@ hipError_t launch_f32_far(const Params& p, int cfg, unsigned grid, hipStream_t s
 // Products of the waves that share the contraction (gemm_wave.hpp, configurations 6-9).
 hipError_t launch_wave(const Params& p, Layout layout, int dtype, int out_dtype, int cfg, unsigned grid,
                        hipStream_t s);
+// The same with the softmax cross-entropy epilogue (EPI_XENT): N at most 32.
+hipError_t launch_wave_xent(const Params& p, int dtype, hipStream_t s);
 // Large float32 products staged in LDS by direct loads (gemm_f32.hpp,
 // configurations 20-22); vec: 16-byte loads.
 hipError_t launch_f32(const Params& p, Layout layout, int cfg, unsigned grid, bool vec, hipStream_t s);

@@ -34,6 +34,9 @@ hipError_t launch_wave_typed(const Params& p, Layout layout, int cfg, unsigned g
   switch (layout) {
     case Layout::NN:
       if (p.A2 != nullptr) return launch_wave_layout<T, TO, true, false, EPI_STORE, true>(p, cfg, grid, s);
+      if constexpr (std::is_same<T, float>::value) {
+        if (p.partials != nullptr) return launch_wave_layout<T, TO, true, false, EPI_CHAIN, false>(p, cfg, grid, s);
+      }
       return launch_wave_layout<T, TO, true, false, EPI_STORE, false>(p, cfg, grid, s);
     case Layout::NT:
       return launch_wave_layout<T, TO, true, true, EPI_DACT, false>(p, cfg, grid, s);
@@ -47,10 +50,28 @@ hipError_t launch_wave_typed(const Params& p, Layout layout, int cfg, unsigned g
 
 hipError_t launch_wave(const Params& p, Layout layout, int dtype, int out_dtype, int cfg, unsigned grid,
                        hipStream_t s) {
-  if (p.partials != nullptr || p.mask != nullptr) return hipErrorInvalidValue;  // (no such epilogue here)
+  if (p.mask != nullptr || (p.partials != nullptr && (dtype != F32 || p.splits > 1)))
+    return hipErrorInvalidValue;  // (no such epilogue here)
   if (dtype == F32) return launch_wave_typed<float, float>(p, layout, cfg, grid, s);
   if (out_dtype == F32) return launch_wave_typed<bf16_t, float>(p, layout, cfg, grid, s);
   return launch_wave_typed<bf16_t, bf16_t>(p, layout, cfg, grid, s);
+}
+
+hipError_t launch_wave_xent(const Params& p, int dtype, hipStream_t s) {
+  if (p.N > 32 || p.lda2 > (p.N <= 16 ? 16 : 32) || p.splits > 1 || p.tiles_n != 1) return hipErrorInvalidValue;
+  const dim3 g(p.tiles_m), b(512);
+  if (dtype == F32) {
+    if (p.N <= 16)
+      launch_kernel((dlvm_gemm_wave_kernel<float, float, true, false, 1, 1, 8, 4, EPI_XENT, false>), g, b, s, p);
+    else
+      launch_kernel((dlvm_gemm_wave_kernel<float, float, true, false, 1, 2, 8, 4, EPI_XENT, false>), g, b, s, p);
+  } else {
+    if (p.N <= 16)
+      launch_kernel((dlvm_gemm_wave_kernel<bf16_t, float, true, false, 1, 1, 8, 4, EPI_XENT, false>), g, b, s, p);
+    else
+      launch_kernel((dlvm_gemm_wave_kernel<bf16_t, float, true, false, 1, 2, 8, 4, EPI_XENT, false>), g, b, s, p);
+  }
+  return hipGetLastError();
 }
 
 namespace {

@@ -262,13 +262,66 @@ constexpr int wave_smem_bytes() {
   return NW * (16 * AB * (16 * BB + 4) + 16 * BB) * 4;
 }
 
+// Softmax cross-entropy of a tile's 16 rows of logits (EPI_XENT; see Params::C2):
+// thread TN r + c takes column c of row r, so a row is 16 or 32 neighbouring lanes.
+// The partial products are summed here (with the bias `b`), so neither the logits
+// nor their slices cross memory between the output layer and its loss. Measured on
+// 10 classes: 256 rows of 512 float32, product and loss 3.6 + 5.0 us before; 4096
+// rows of 1024 bf16, 6.2 + 3.9.
+template <typename T, int TN, int NW>
+__device__ __forceinline__ void wave_xent(const Params& p, const float* part, float* rowv, int ld,
+                                          int64_t m0, int tile, int tid, float b) {
+  constexpr int TM = 16;
+  const int r = tid / TN, c = tid % TN;
+  const int64_t row = m0 + r;
+  const bool in = tid < TM * TN, live = in && row < p.M, valid = live && c < p.N;
+  float z = 0.0f;
+  if (in) {
+    z = part[r * ld + c];
+#pragma unroll
+    for (int w = 1; w < NW; ++w) z += part[w * TM * ld + r * ld + c];
+    z = p.alpha * z + b;
+  }
+  const int y = live ? static_cast<const int32_t*>(p.aux)[row] : 0;
+  const bool ok = y >= 0 && y < p.N;
+  float m = row16_max(valid ? z : -INFINITY);
+  if constexpr (TN == 32) m = fmaxf(m, __shfl_xor(m, 16, 64));
+  const float e = valid ? __expf(z - m) : 0.0f;
+  float s = row16_sum(e), zy = row16_sum(valid && c == y ? z : 0.0f);  // (one term: exact)
+  if constexpr (TN == 32) {
+    s += __shfl_xor(s, 16, 64);
+    zy += __shfl_xor(zy, 16, 64);
+  }
+  if (live && c < p.lda2) {
+    const float d = valid ? p.inv_n / s * e - (c == y ? p.inv_n : 0.0f) : 0.0f;
+    static_cast<T*>(p.C2)[row * p.lda2 + c] = store_cast<T>(d);
+  }
+  if (valid && p.C != nullptr) static_cast<float*>(p.C)[row * p.ldc + c] = z;
+  if (in && c == 0) {
+    rowv[r] = !live ? 0.0f : ok ? (m + __logf(s)) - zy : NAN;
+    reinterpret_cast<int*>(rowv)[TM + r] = live && !ok ? 1 : 0;
+  }
+  __syncthreads();
+  if (tid == 0) {
+    float t = 0.0f;
+    int bad = 0;
+#pragma unroll
+    for (int q = 0; q < TM; ++q) {
+      t += rowv[q];
+      bad += reinterpret_cast<const int*>(rowv)[TM + q];
+    }
+    p.partials[tile] = t;
+    static_cast<int32_t*>(const_cast<void*>(p.residual))[tile] = bad;
+  }
+}
+
 // One output tile (`tile` from split_slice) of a product, LDS at `smem`. EDGE:
 // the tile crosses the edge of the output; ONE: a row-contiguous operand has fewer
 // columns left than one load takes, so values are loaded one by one.
 template <typename T, typename TO, bool AK, bool BKM, int AB, int BB, int NW, int DEPTH, int EPI,
           bool PH2, bool EDGE, bool ONE>
 __device__ __forceinline__ void wave_gemm_body(const Params& p, int64_t m0, int64_t n0, int tm,
-                                               char* smem) {
+                                               int tile, char* smem) {
   constexpr int TM = 16 * AB, TN = 16 * BB, LD = TN + 4;
   constexpr int THREADS = 64 * NW, STEP = wave_step<T>();
   const int tid = threadIdx.x, lane = tid & 63;
@@ -286,13 +339,14 @@ __device__ __forceinline__ void wave_gemm_body(const Params& p, int64_t m0, int6
   const T* const aux = static_cast<const T*>(p.aux);
   const TO* const res = static_cast<const TO*>(p.residual);
   const T* const bias = static_cast<const T*>(p.bias);
-  const bool use_aux = EPI == EPI_DACT && p.act != ACT_NONE;
+  const bool use_aux = EPI == EPI_CHAIN || (EPI == EPI_DACT && p.act != ACT_NONE);
   const bool use_res = EPI == EPI_DACT && res != nullptr;
   auto fetch = [&](int j, float& b, float& gr, float& r) {
     const int o = tid + j * THREADS;
     const int64_t row = m0 + o / TN, col = n0 + o % TN;
     const bool in = o < TM * TN && (!EDGE || (row < p.M && col < p.N));
-    b = EPI == EPI_STORE && bias != nullptr && in && col < p.nvec ? load_as_f32<T>(bias + col) : 0.0f;
+    constexpr bool BIAS = EPI == EPI_STORE || EPI == EPI_CHAIN || EPI == EPI_XENT;
+    b = BIAS && bias != nullptr && in && col < p.nvec ? load_as_f32<T>(bias + col) : 0.0f;
     gr = use_aux && in ? load_as_f32<T>(aux + row * p.ldc + col) : 0.0f;
     r = use_res && in ? load_as_f32<TO>(res + row * p.ldc + col) : 0.0f;
   };
@@ -479,6 +533,12 @@ __device__ __forceinline__ void wave_gemm_body(const Params& p, int64_t m0, int6
   __syncthreads();
 
   TO* const C = static_cast<TO*>(p.C);
+  if constexpr (EPI == EPI_XENT) {
+    static_assert(AB == 1 && BB <= 2 && AHEAD && TM * TN <= THREADS, "one output per thread, rows of 16 or 32 lanes");
+    wave_xent<T, TN, NW>(p, part, cpart, LD, m0, tile, tid, pre_b[0]);
+    return;
+  }
+  float sq = 0.0f;  // EPI_CHAIN: this thread's sum of e^2
 #pragma unroll
   for (int j = 0; j < PER; ++j) {
     const int o = tid + j * THREADS;
@@ -495,7 +555,11 @@ __device__ __forceinline__ void wave_gemm_body(const Params& p, int64_t m0, int6
     } else {
       fetch(j, bv, gv, rv);
     }
-    if constexpr (EPI == EPI_STORE) {
+    if constexpr (EPI == EPI_CHAIN) {
+      float xb, e;
+      sq += chain_elem(v, bv, gv, p.inv_n, false, v, xb, e);
+      static_cast<float*>(p.C2)[row * p.ldc + col] = xb;
+    } else if constexpr (EPI == EPI_STORE) {
       v = apply_act(p.act, p.alpha * v + bv);
     } else if constexpr (EPI == EPI_DACT) {
       if (p.res_pre) v += rv;
@@ -503,6 +567,19 @@ __device__ __forceinline__ void wave_gemm_body(const Params& p, int64_t m0, int6
       if (!p.res_pre) v += rv;
     }
     C[row * p.ldc + col] = store_cast<TO>(v);
+  }
+  if constexpr (EPI == EPI_CHAIN) {
+    // one loss partial per tile: butterflies, then the waves in order
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) sq += __shfl_xor(sq, o, 64);
+    if (lane == 0) cpart[wave] = sq;
+    __syncthreads();
+    if (tid == 0) {
+      float t = cpart[0];
+#pragma unroll
+      for (int w = 1; w < NW; ++w) t += cpart[w];
+      p.partials[tile] = t;
+    }
   }
   if constexpr (EPI == EPI_DW) {
     if (do_colsum && tid < TN && n0 + tid < p.nvec) {
@@ -522,13 +599,13 @@ __device__ __forceinline__ void wave_gemm_tile(const Params& p, int tile, char* 
   const int64_t m0 = static_cast<int64_t>(tm) * (16 * AB);
   const int64_t n0 = static_cast<int64_t>(tn) * (16 * BB);
   if (m0 + 16 * AB <= p.M && n0 + 16 * BB <= p.N) {
-    wave_gemm_body<T, TO, AK, BKM, AB, BB, NW, DEPTH, EPI, PH2, false, false>(p, m0, n0, tm, smem);
+    wave_gemm_body<T, TO, AK, BKM, AB, BB, NW, DEPTH, EPI, PH2, false, false>(p, m0, n0, tm, tile, smem);
   } else {
     constexpr bool CA = !AK && AB > 1, CB = !BKM && BB > 1;  // loads of several columns
     if ((CA && p.M - m0 < AB) || (CB && p.N - n0 < BB))
-      wave_gemm_body<T, TO, AK, BKM, AB, BB, NW, DEPTH, EPI, PH2, true, CA || CB>(p, m0, n0, tm, smem);
+      wave_gemm_body<T, TO, AK, BKM, AB, BB, NW, DEPTH, EPI, PH2, true, CA || CB>(p, m0, n0, tm, tile, smem);
     else
-      wave_gemm_body<T, TO, AK, BKM, AB, BB, NW, DEPTH, EPI, PH2, true, false>(p, m0, n0, tm, smem);
+      wave_gemm_body<T, TO, AK, BKM, AB, BB, NW, DEPTH, EPI, PH2, true, false>(p, m0, n0, tm, tile, smem);
   }
 }
 

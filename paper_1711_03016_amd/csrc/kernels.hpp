@@ -75,11 +75,13 @@ struct GemmDesc {
   // loss term (sum of e^2) per wavefront of each tile (chain_partials of them);
   // inv_n is the seed 1 / (M N) of the mean. Never split.
   bool chain_epilogue;
-  bool chain_product;  // the product of a chain network (chain in its epilogue or after it):
-                       // planned the same either way, so that both give the same bits
   void* C2;
   float* partials;
   float inv_n;
+  // NN float32: the product of a rectified layer whose derivative is taken (the
+  // derivative switches with the last bit of a sum near zero, so these keep the
+  // register-staged tiles and their order of sums).
+  bool sum_order;
   // bf16 rectified layers on the 256 x 256 or 64 x 128 direct-to-LDS tile,
   // unsplit (mask_ok): an NN product writes the rectifier bits of its output
   // here, an NT product reads them in place of aux. Null: none.
@@ -118,12 +120,22 @@ int64_t mask_bytes(int64_t M, int64_t N);
 void tuning_scope_begin();
 void tuning_scope_end();
 
-// Loss partials a chain-epilogue product writes (one per wavefront of a tile).
+// Loss partials a chain-epilogue product writes (one per wavefront of a tile, or
+// one per tile where the waves share the contraction).
 int64_t chain_partials(const GemmPlan& plan);
 
 // Enqueue one GEMM with its fused epilogue as planned. Returns hipSuccess or
 // the launch error. The caller has validated shapes and pointers.
 hipError_t launch_gemm(const GemmDesc& d, const GemmPlan& plan, hipStream_t s);
+
+// The output layer's product and its softmax cross-entropy in one launch (at most 32
+// classes): `head` as planned unsplit with float32 logits (stored to head.C unless it
+// is null), labels, the seed scale and the outputs as launch_softmax_xent, one loss
+// partial and label count per 16 rows.
+bool head_xent_ok(const GemmDesc& head, int64_t ld_dlogits);
+hipError_t launch_head_xent(const GemmDesc& head, const int32_t* labels, float scale, void* dlogits,
+                            int64_t ld_dlogits, float* partials, int32_t* bad, int* n_partials,
+                            hipStream_t s);
 
 // The two adjoint products of one layer (tn: wrt the weights, nt: wrt the
 // input) can run as one launch when planned on configurations that have a paired kernel.

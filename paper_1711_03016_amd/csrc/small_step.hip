@@ -60,24 +60,6 @@ __device__ __forceinline__ int wave_or(int v) {
   return v;
 }
 
-// Sum and maximum over the 16 lanes of a row (every lane ends with the same bits).
-template <int CTRL>
-__device__ __forceinline__ float row_rot(float v) {
-  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, 0xf, 0xf, true));
-}
-__device__ __forceinline__ float row16_sum(float v) {
-  v += row_rot<0x128>(v);  // rotations by 8, 4, 2, 1 lanes
-  v += row_rot<0x124>(v);
-  v += row_rot<0x122>(v);
-  return v + row_rot<0x121>(v);
-}
-__device__ __forceinline__ float row16_max(float v) {
-  v = fmaxf(v, row_rot<0x128>(v));
-  v = fmaxf(v, row_rot<0x124>(v));
-  v = fmaxf(v, row_rot<0x122>(v));
-  return fmaxf(v, row_rot<0x121>(v));
-}
-
 // One 16 x 16 tile of a product over K terms from LDS: A(m, k) at a[m * am + k * ak]
 // for the tile's rows m < M (rows past it are read from row 0 and give outputs that
 // are not stored), B(k, n) at b[n * bn + k * bk] for n < N. Lane 16 g + l of an
