@@ -770,8 +770,8 @@ dlvm_status plan_gradient(const dlvm_model* m, const void* params, const void* x
 
 // The launches of one seedable gradient call (Fig. 3's seedable
 // declaration, wrt the parameters [and x]): the hidden layers' forward keeping
-// their outputs, the seed stored as the output layer's adjoint, the adjoint
-// sweep, the padding of dparams zeroed. The output layer's own product is
+// their outputs, the seed stored as the output layer's adjoint (the same launch zeroes
+// the padding of dparams), the adjoint sweep. The output layer's own product is
 // dead (its value is not kept) and is not computed.
 dlvm_status plan_vjp(const dlvm_model* m, const void* params, const void* x, const float* seed,
                      int64_t batch, float* dparams, float* dx, void* ws, Launcher& run) {
@@ -783,17 +783,11 @@ dlvm_status plan_vjp(const dlvm_model* m, const void* params, const void* x, con
   const int64_t C = m->widths[L], ldc = m->ldw[L - 1];
   st = run.run([&] { return elementwise_info("seed", batch, C, double(batch) * (4.0 * C + elem_size(dt) * ldc)); },
                [&](hipStream_t s) {
-                 return dlvm::launch_seed(dt, batch, C, ldc, seed, at<void>(ws, w.dz[L - 1]), s);
+                 return dlvm::launch_seed(dt, batch, C, ldc, seed, at<void>(ws, w.dz[L - 1]), dparams, m->gaps, s);
                },
                "seed launch");
   if (st != DLVM_OK) return st;
-  if ((st = plan_adjoint_layers(m, params, x, batch, dparams, dx, ws, w, run)) != DLVM_OK) return st;
-  return run.run([&] { return elementwise_info("zero_padding", 0, 1, 4.0 * m->param_count); },
-                 [&](hipStream_t s) {
-                   return dlvm::launch_finalize(nullptr, nullptr, 0, 1.0f, nullptr, nullptr, dparams,
-                                                m->gaps, s);
-                 },
-                 "padding launch");
+  return plan_adjoint_layers(m, params, x, batch, dparams, dx, ws, w, run);
 }
 
 // The launches of one forward call: nothing is kept; layer l's output goes to
@@ -986,7 +980,8 @@ dlvm_status plan_rnn_backward(const dlvm_model* m, const void* params, const voi
   dlvm_status st = run.run(
       [&] { return elementwise_info("act_adjoint", B, H, 3.0 * double(B) * H * es); }, [&](hipStream_t s) {
         return dlvm::launch_act_adjoint(dt, m->acts[0], B * H, seq_at(dhs, T - 1, B, H, es),
-                                        seq_at(hs, T, B, H, es), seq_at(dz, T - 1, B, H, es), s);
+                                        seq_at(hs, T, B, H, es), seq_at(dz, T - 1, B, H, es),
+                                        dparams, m->gaps, s);
       },
       "activation adjoint launch");
   if (st != DLVM_OK) return st;
@@ -1014,13 +1009,7 @@ dlvm_status plan_rnn_backward(const dlvm_model* m, const void* params, const voi
     st = run.gemm(dw);
   }
   if (st != DLVM_OK) return st;
-  if ((st = run.gemm(du)) != DLVM_OK) return st;
-  return run.run([&] { return elementwise_info("zero_padding", 0, 1, 4.0 * m->param_count); },
-                 [&](hipStream_t s) {
-                   return dlvm::launch_finalize(nullptr, nullptr, 0, 1.0f, nullptr, nullptr, dparams,
-                                                m->gaps, s);
-                 },
-                 "padding launch");
+  return run.gemm(du);
 }
 
 // The launches of one training step up to the update, without running them:

@@ -214,9 +214,11 @@ double estimate(const GemmDesc& d, const TileShape& t, int splits, bool aligned)
       const int64_t kstage = int64_t(t.kseg) * 64;
       per_tile = std::max(per_tile, double(ceil_div(kc, kstage)) * kStageCycles);
     }
-    // (wrt the weights, whole, at most one tile per compute unit: 2048 x 512 x 512 on
-    // 12 25,000 cycles measured, 11,600 without)
-    if (t.async && d.layout == Layout::TN && slices == 1 && tiles <= kComputeUnits) per_tile *= 1.25;
+    // (wrt the weights, whole, at most one small tile per compute unit: 2048 x 512 x
+    // 512 on 12 25,000 cycles measured, 11,600 without; the 256 x 256 tiles of a
+    // 4096 x 4096 output fill the chip at this rate)
+    if (t.async && t.bm * t.bn <= 128 * 128 && d.layout == Layout::TN && slices == 1 && tiles <= kComputeUnits)
+      per_tile *= 1.25;
     per_tile += kTileFixed;
     c = double(ceil_div(tiles * slices, kComputeUnits)) * per_tile;
     if (!aligned) c += 6000.0;  // (launch: the waves' estimate counts it for such products)

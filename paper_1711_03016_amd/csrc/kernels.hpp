@@ -170,7 +170,7 @@ int chain8_partials(int64_t rows, int64_t cols);
 
 // Sum `n` partials in a fixed order, multiply by `scale`, write *out. Writes
 // flags[0] = (any bad label counted in `bad`, which may be null) and
-// flags[1] = (loss not finite) on every call. With out == null only zeroes.
+// flags[1] = (loss not finite) on every call.
 // Zeroes the `gaps` ranges of `zero_base` (may be null).
 struct ZeroGaps {
   static constexpr int kMax = 64;
@@ -187,8 +187,9 @@ hipError_t launch_sgd(int dtype, int64_t n, void* params, float* master, const f
 
 // dz[r, c] (row stride ld, storage dtype) = seed[r, c] for c < classes, 0 for
 // classes <= c < ld.
+// Also zeroes the `gaps` ranges of `zero_base`.
 hipError_t launch_seed(int dtype, int64_t rows, int64_t classes, int64_t ld, const float* seed,
-                       void* dz, hipStream_t s);
+                       void* dz, float* zero_base, const ZeroGaps& gaps, hipStream_t s);
 
 // Sum of the k-slices of a split NN (mode 0) or NT (mode 1) product in slice
 // order, then its epilogue: mode 0 out = act(alpha * sum + bias[c]) (bias for
@@ -237,9 +238,9 @@ hipError_t launch_small_step(const SmallNet& t, const float* params, const float
                              int32_t* flags, const ZeroGaps& gaps, hipStream_t s);
 
 // out[i] = g[i] * act'(h[i]) for i < n, act' from the saved output h = act(z)
-// (storage dtype `dtype` for all three).
+// (storage dtype `dtype` for all three). Also zeroes the `gaps` ranges of `zero_base`.
 hipError_t launch_act_adjoint(int dtype, int act, int64_t n, const void* g, const void* h,
-                              void* out, hipStream_t s);
+                              void* out, float* zero_base, const ZeroGaps& gaps, hipStream_t s);
 
 // Sum of the k-slices of a split product in slice order: out[r, c] (row
 // stride ld) = sum_s part[s * c_split + r * ld + c] for c < cols, and
