@@ -22,7 +22,7 @@ constexpr double kL2BytesPerClock = 64.0;
 // Configurations 0-5 are the register-staged kernel (gemm_kernel.hpp), 10-13, 16
 // and 17 the bf16 kernel with direct-to-LDS loads (gemm_async.hpp; 18 and 19 with
 // two k-groups of waves), 14-15 the four-wave bf16 kernel (gemm_xl.hpp). Float32
-// products run on 6-9 (gemm_wave.hpp) and 20-22 (gemm_f32.hpp); 0-4 are left to
+// products run on 6-9 and 23 (gemm_wave.hpp) and 20-22 (gemm_f32.hpp); 0-4 are left to
 // the forward products that keep their order of sums (GemmDesc::sum_order), and 3
 // to leading dimensions whose byte offsets the others cannot hold.
 struct TileShape {
@@ -39,7 +39,8 @@ constexpr TileShape kTiles[] = {
     {13, 256, 256, 0.88, true, 0}, {14, 256, 256, 0.89, true, 0}, {15, 256, 256, 0.85, true, 0},
     {16, 64, 128, 0.5, true, 0},   {17, 128, 128, 0.54, true, 0}, {18, 64, 128, 0.55, true, 0},
     {19, 128, 128, 0.56, true, 0}, {20, 128, 128, 0.0, false, 0}, {22, 128, 64, 0.0, false, 0},
-    {21, 64, 64, 0.0, false, 0},   {9, 64, 64, 0.0, false, 0},    {8, 32, 32, 0.0, false, 0},
+    {21, 64, 64, 0.0, false, 0},   {9, 64, 64, 0.0, false, 0},    {23, 32, 64, 0.0, false, 0},
+    {8, 32, 32, 0.0, false, 0},
     {7, 16, 32, 0.0, false, 0},    {6, 16, 16, 0.0, false, 0}};
 
 // The register-staged kernel has one stage of loads in flight: a stage costs
@@ -116,9 +117,9 @@ bool xl_phases_ok(const GemmDesc& d) {
          d.N <= d.ldb;
 }
 
-// The kernel that loads its fragments from global memory (configurations 6-9): any
+// The kernel that loads its fragments from global memory (configurations 6-9, 23): any
 // size and alignment; the byte offsets inside a step (up to 64 rows) stay below 2^31.
-bool wave_config(int cfg) { return cfg >= 6 && cfg <= 9; }
+bool wave_config(int cfg) { return (cfg >= 6 && cfg <= 9) || cfg == 23; }
 bool wave_ok(const GemmDesc& d) {
   const int64_t lim = int64_t(1) << 22;
   return !d.sum_order && d.mask == nullptr && d.lda <= lim && d.ldb <= lim &&
@@ -143,7 +144,7 @@ int64_t slice_k(int64_t K, int splits) { return ceil_div(ceil_div(K, splits), 64
 // matrix-core cycles (256 flops a cycle) times what the kernel takes over them,
 // plus launch, first loads and epilogue. Fitted to back-to-back launches of
 // 8 x 64 x 64 to 8192 x 4096 x 4096 (2,400 cycles a us). Waves that share the
-// contraction (6-9): the smaller the tile, the more the operand loads weigh,
+// contraction (6-9, 23): the smaller the tile, the more the operand loads weigh,
 // most where both operands are k-contiguous (NT: each 16-byte load of a wave
 // touches 16 rows). Tiles in LDS (20-22): at 1.1-1.2 times the matrix cycles once
 // several tiles share a compute unit, far from it with one.
@@ -156,6 +157,7 @@ double estimate_f32(const GemmDesc& d, const TileShape& t, int64_t slots, int64_
     case 6: { const double o[] = {2.7, 4.0, 2.5}; over = o[lay]; break; }
     case 7: { const double o[] = {2.3, 3.1, 1.9}; over = o[lay]; break; }
     case 8: { const double o[] = {1.9, 2.7, 1.7}; over = o[lay]; break; }
+    case 23: { const double o[] = {1.8, 2.2, 1.55}; over = o[lay]; break; }
     case 9: { const double o[] = {1.6, 1.65, 1.4}; over = o[lay]; break; }
     case 20: over = 1.08 + 0.4 / rounds; fixed = 8000.0; break;
     case 22: over = 1.13 + 0.55 / rounds; fixed = 8000.0; break;
@@ -165,7 +167,7 @@ double estimate_f32(const GemmDesc& d, const TileShape& t, int64_t slots, int64_
   return fixed + rounds * mfma * over;
 }
 
-// The same for a bf16 product on the waves that share the contraction (6-9): per
+// The same for a bf16 product on the waves that share the contraction (6-9, 23): per
 // round a fixed part (first loads, partial tiles through LDS) and its operands at
 // the bytes per cycle measured for each layout, on 64 x 256 x 356 to
 // 4096 x 1024 x 1024; times 1.5 where rows start anywhere (2049-element rows and
@@ -175,10 +177,10 @@ double estimate_f32(const GemmDesc& d, const TileShape& t, int64_t slots, int64_
 // against 59,500 measured, 25 us on either kernel), the others, with at most one
 // tile per compute unit, 1.8 times (1024 x 1024 x 2048 on 12: 34,000 against 63,000).
 double estimate_wave_bf16(const GemmDesc& d, const TileShape& t, int64_t slots, int64_t kc, bool aligned) {
-  static const double fix[] = {1400.0, 2000.0, 2500.0, 10000.0};
-  static const double rate[4][3] = {  // NN, NT, TN
-      {18.0, 15.0, 11.0}, {15.0, 16.0, 15.0}, {16.0, 14.0, 17.0}, {17.0, 13.0, 24.0}};
-  const int i = t.cfg - 6;
+  static const double fix[] = {1400.0, 2000.0, 2500.0, 8000.0, 3500.0};
+  static const double rate[5][3] = {  // NN, NT, TN
+      {18.0, 15.0, 11.0}, {15.0, 16.0, 15.0}, {16.0, 14.0, 17.0}, {17.0, 14.0, 24.0}, {20.0, 15.0, 18.0}};
+  const int i = t.cfg == 23 ? 4 : t.cfg - 6;
   const double rounds = double(ceil_div(slots, kComputeUnits));
   const double bytes = double(t.bm + t.bn) * double(kc) * 2.0;
   const double c = rounds * (fix[i] + bytes / rate[i][static_cast<int>(d.layout)]);

@@ -778,7 +778,7 @@ hipError_t launch_f32_far(const Params& p, int cfg, unsigned grid, hipStream_t s
   return hipGetLastError();
 }
 
-// Products of the waves that share the contraction (gemm_wave.hpp, configurations 6-9).
+// Products of the waves that share the contraction (gemm_wave.hpp, configurations 6-9, 23).
 hipError_t launch_wave(const Params& p, Layout layout, int dtype, int out_dtype, int cfg, unsigned grid,
                        hipStream_t s);
 // The same with the softmax cross-entropy epilogue (EPI_XENT): N at most 32.

@@ -7,9 +7,9 @@ namespace dlvm {
 namespace gemm {
 
 bool pair_config(int dtype, int cfg_tn, int cfg_nt) {
-  // (6, 7 and 8 have the same number of waves, so any two of them share a launch)
-  const bool w1 = cfg_tn >= 6 && cfg_tn <= 8, w2 = cfg_nt >= 6 && cfg_nt <= 8;
-  if (w1 && w2) return true;
+  // (6, 7, 8 and 23 have the same number of waves, so any two of them share a launch)
+  auto eight = [](int c) { return (c >= 6 && c <= 8) || c == 23; };
+  if (eight(cfg_tn) && eight(cfg_nt)) return true;
   if (cfg_tn != cfg_nt) return false;
   if (cfg_tn == 9) return true;
   if (dtype == F32) return cfg_tn >= 20 && cfg_tn <= 22;

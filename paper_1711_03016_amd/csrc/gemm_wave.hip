@@ -8,6 +8,16 @@ namespace gemm {
 
 namespace {
 
+// Waves of the 64 x 64 tile (configuration 9). bf16 is bound by the loads in flight of
+// the one tile a compute unit has (1024 x 1024 x 4096 wrt the weights: 23.1 us with 4
+// waves, 21.2 with 8); float32 tiles are several to a unit, and 8 waves' partial tiles
+// would leave LDS for one (2048 x 1024 x 768: 34.6 us with 4 waves, 38.3 with 8).
+//
+// Between it and 32 x 32 (8) stands 32 x 64 (23): forward 1000 x 500 x 784 in bf16 has 256
+// such tiles, one to a compute unit, and takes 7.1 us (8: 512 tiles, 8.2; 9: 128 tiles,
+// 10.5); float32 777 x 1001 x 2049 wrt the weights 41.4 (8: 45.2; 9: 40.0).
+template <typename T> constexpr int kNW9 = sizeof(T) == 2 ? 8 : 4;
+
 template <typename T, typename TO, bool AK, bool BKM, int EPI, bool PH2>
 hipError_t launch_wave_layout(const Params& p, int cfg, unsigned grid, hipStream_t s) {
   switch (cfg) {
@@ -21,7 +31,11 @@ hipError_t launch_wave_layout(const Params& p, int cfg, unsigned grid, hipStream
       launch_kernel((dlvm_gemm_wave_kernel<T, TO, AK, BKM, 2, 2, 8, 3, EPI, PH2>), dim3(grid), dim3(512), s, p);
       break;
     case 9:
-      launch_kernel((dlvm_gemm_wave_kernel<T, TO, AK, BKM, 4, 4, 4, 2, EPI, PH2>), dim3(grid), dim3(256), s, p);
+      launch_kernel((dlvm_gemm_wave_kernel<T, TO, AK, BKM, 4, 4, kNW9<T>, 2, EPI, PH2>), dim3(grid),
+                    dim3(64 * kNW9<T>), s, p);
+      break;
+    case 23:
+      launch_kernel((dlvm_gemm_wave_kernel<T, TO, AK, BKM, 2, 4, 8, 3, EPI, PH2>), dim3(grid), dim3(512), s, p);
       break;
     default:
       return hipErrorInvalidValue;
@@ -86,6 +100,9 @@ hipError_t launch_wave_pair(const Params& p1, const Params& p2, int n1, unsigned
     case 7:
       launch_kernel((dlvm_gemm_wave_pair_kernel<T, TO2, AB1, BB1, D1, 1, 2, 4, 8>), dim3(grid), dim3(512), s, p1, p2, n1);
       break;
+    case 23:
+      launch_kernel((dlvm_gemm_wave_pair_kernel<T, TO2, AB1, BB1, D1, 2, 4, 3, 8>), dim3(grid), dim3(512), s, p1, p2, n1);
+      break;
     default:
       launch_kernel((dlvm_gemm_wave_pair_kernel<T, TO2, AB1, BB1, D1, 2, 2, 3, 8>), dim3(grid), dim3(512), s, p1, p2, n1);
       break;
@@ -120,8 +137,10 @@ hipError_t launch_wave_pair_typed(const Params& p1, const Params& p2, int n1, un
     case 6: return launch_wave_pair<T, TO2, 1, 1, 4>(p1, p2, n1, grid, cfg_nt, s);
     case 7: return launch_wave_pair<T, TO2, 1, 2, 4>(p1, p2, n1, grid, cfg_nt, s);
     case 8: return launch_wave_pair<T, TO2, 2, 2, 3>(p1, p2, n1, grid, cfg_nt, s);
+    case 23: return launch_wave_pair<T, TO2, 2, 4, 3>(p1, p2, n1, grid, cfg_nt, s);
     default:
-      launch_kernel((dlvm_gemm_wave_pair_kernel<T, TO2, 4, 4, 2, 4, 4, 2, 4>), dim3(grid), dim3(256), s, p1, p2, n1);
+      launch_kernel((dlvm_gemm_wave_pair_kernel<T, TO2, 4, 4, 2, 4, 4, 2, kNW9<T>>), dim3(grid),
+                    dim3(64 * kNW9<T>), s, p1, p2, n1);
       return hipGetLastError();
   }
 }

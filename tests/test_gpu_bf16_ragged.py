@@ -1,5 +1,5 @@
 """bf16 products whose rows start anywhere: the waves that share the contraction
-(6-9, gemm_wave.hpp) and the register-staged tiles (0-5), each configuration forced,
+(6-9 and 23, gemm_wave.hpp) and the register-staged tiles (0-5), each configuration forced,
 in all three layouts and the two-phase cell product, at sizes that no 16-byte load
 divides (chunks shifted into place at the end of a row, element loads for rows
 shorter than a chunk), between NaNs that must reach no output.
@@ -16,7 +16,7 @@ from helpers import device, quant, to_np
 
 pytestmark = pytest.mark.gpu
 
-CFGS = [0, 1, 2, 3, 4, 5, 6, 7, 8, 9]
+CFGS = [0, 1, 2, 3, 4, 5, 6, 7, 8, 9, 23]
 # (M, N, K): one element, rows shorter than a chunk, exactly one, one more; odd sizes past
 # one tile of each configuration; sizes that aligned loads take; many steps
 SHAPES = [(1, 1, 1), (3, 5, 7), (9, 8, 9), (33, 17, 70), (129, 65, 131), (70, 257, 63), (64, 96, 256),

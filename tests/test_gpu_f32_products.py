@@ -1,5 +1,5 @@
 """The float32 product kernels, every tile configuration forced: the waves that
-share the contraction (6-9, gemm_wave.hpp), the tiles staged in LDS (20-22,
+share the contraction (6-9 and 23, gemm_wave.hpp), the tiles staged in LDS (20-22,
 gemm_f32.hpp) and the element-load fallback for leading dimensions beyond their
 byte offsets (3), in all three layouts and the two-phase cell product.
 
@@ -17,7 +17,7 @@ from helpers import assert_close, device, to_dev, to_np
 
 pytestmark = pytest.mark.gpu
 
-CFGS = [6, 7, 8, 9, 20, 21, 22]
+CFGS = [6, 7, 8, 9, 20, 21, 22, 23]
 # (M, N, K): smaller than one step and one tile, exact tiles, one past a tile in every
 # size, sizes that no vector load divides, fewer steps than waves, many k-tiles
 SHAPES = [(1, 1, 1), (5, 3, 7), (128, 128, 32), (129, 65, 33), (17, 33, 130), (64, 130, 64),

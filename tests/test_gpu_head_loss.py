@@ -72,7 +72,7 @@ def test_label_out_of_range(classes, label):
     assert (dz[77] > 0).all() and ((dz < 0).sum(axis=1) == 1).sum() == 99
 
 
-@pytest.mark.parametrize("cfg", [6, 7, 8, 9, 20, 21, 22])
+@pytest.mark.parametrize("cfg", [6, 7, 8, 9, 20, 21, 22, 23])
 @pytest.mark.parametrize("n,batch", [(37, 50), (200, 300)])
 def test_chain_in_epilogue_on_every_tile(cfg, n, batch, monkeypatch):
     import torch
