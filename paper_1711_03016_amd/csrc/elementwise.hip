@@ -383,7 +383,7 @@ __global__ __launch_bounds__(kBlock) void dlvm_chain8_kernel(
 // One workgroup, so its time is round trips: 16 waves with four loads of each
 // array in flight per thread (4,096 partials at once; one load at a time by 256
 // threads took 16 round trips, 6.1 us for the 4,096 partials of a 16384-row loss
-// against 3.0 now), and the gaps shared out over the waves (one after the other, each
+// against 3.8 now), and the gaps shared out over the waves (one after the other, each
 // with its kernel-argument reads, 4.6 us for six gaps).
 // ---------------------------------------------------------------------------
 constexpr int kFinBlock = 1024;
@@ -500,8 +500,10 @@ __device__ __forceinline__ void load4f<bf16_t>(const bf16_t* p, float (&v)[4]) {
 
 // Sum of S k-slices (c_split floats apart) in slice order, S0 of them (0: any number)
 // known to the compiler, so that all loads of up to 8 slices are in flight at once:
-// with the number at run time each load waited for the one before (four slices of
-// 1024 x 1024 5.2 us against 3.6; two with an epilogue 4.9 against 4.0).
+// with the number at run time each load waited for the one before. Where few waves
+// hide that it is most of the time (eight slices of 1024 x 16: 4.3 us, now 2.9); many
+// waves hide it (two slices of 1024 x 1024 with an epilogue 4.84 us, now 4.70; four
+// without 5.1, bound by their 21 MB).
 template <int S0>
 __device__ __forceinline__ float4 sum_slices4(const float* p, int64_t c_split, int S) {
   constexpr int U = S0 > 0 && S0 < 8 ? S0 : 8;

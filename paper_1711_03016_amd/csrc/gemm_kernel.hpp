@@ -1,6 +1,11 @@
-// Dense-layer matrix products on gfx950 matrix cores, with fused epilogues.
+// Dense-layer matrix products on gfx950 matrix cores, with fused epilogues: the
+// register-staged kernel. bf16 products whose rows are not 16-byte aligned run on it
+// from 64 x 64 tiles up (aligned ones on gemm_async.hpp, small ones on
+// gemm_wave.hpp), and the float32 forward products that keep their order of sums
+// (GemmDesc::sum_order); the other float32 products run on gemm_wave.hpp and
+// gemm_f32.hpp.
 //
-// The one kernel template computes C[M,N] = sum_k A(m,k) B(k,n) for the three
+// The kernel template computes C[M,N] = sum_k A(m,k) B(k,n) for the three
 // operand layouts a dense layer and its adjoint need (the adjoint of dot,
 // dA = dC.B^T and dB = A^T.dC, never materialises a transpose):
 //   NN  forward               A = X [M,K] (k contiguous), B = W [K,N] (n contiguous)
@@ -16,9 +21,8 @@
 //
 // Data movement. Every operand tile is staged in LDS as rows of 128 bytes of
 // the reduction dimension (32 float32 or 64 bf16), one row per m (or n)
-// index, padded to a 144-byte stride. Global loads are 16 bytes per lane when
-// the operand's contiguous extent allows it (per operand), else element by
-// element with bounds checks. An operand whose reduction dimension is strided
+// index, padded to a 144-byte stride. Global loads are 16 bytes per lane at any
+// alignment; element by element where a row is shorter than that. An operand whose reduction dimension is strided
 // in memory (the TN layout, and W in the NN layout) is transposed in registers
 // on its way to LDS (4x4 float32 blocks are a register renaming; 8x8 bf16
 // blocks use byte permutes), so the MFMA fragment of every lane is one
@@ -665,20 +669,6 @@ __device__ __forceinline__ void gemm_tile(Params& p, const int tile, char* smem)
   }
 
   // Epilogue.
-  if constexpr (EPI == EPI_CHAIN) {
-    // Each wavefront's e^2 sum (fixed-order butterfly) is one loss partial:
-    // no synchronisation between the wavefronts of the tile.
-    float sq = 0.0f;
-#pragma unroll
-    for (int j = 0; j < TN; ++j)
-#pragma unroll
-      for (int i = 0; i < TM; ++i)
-        sq += chain_block(p, acc[i][j], m0 + wm * WTM + i * 32, n0 + wn * WTN + j * 32, lane);
-#pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) sq += __shfl_xor(sq, o, 64);
-    if (lane == 0) p.partials[static_cast<int64_t>(tile) * (WM * WN) + wmn] = sq;
-    return;
-  }
 #pragma unroll
   for (int j = 0; j < TN; ++j)
 #pragma unroll

@@ -16,7 +16,7 @@
 // and the operands cross no LDS. Measured back to back in float32 (rotating
 // operands): 256 x 512 x 784 12.7 -> 5.8 us, 256 x 512 x 512 9.3 -> 4.3;
 // 64 x 256 x 356 (a recurrent cell) 8.1 -> 3.3; 512 x 512 x 256 wrt the weights
-// 6.8 -> 4.2. In bf16: 1000 x 500 x 784 (rows of 500) 45 -> 9.6, 4096 x 10 x 1024
+// 6.8 -> 4.2. In bf16: 1000 x 500 x 784 (rows of 500) 45 -> 7.1, 4096 x 10 x 1024
 // 11.3 -> 5.0, 1024 x 16 x 4096 wrt the weights 11.4 (in slices, with their sum) -> 7.3.
 //
 // Fragments without LDS. v_mfma_f32_16x16x4_f32 wants, in lane 16 g + l, the value
