@@ -81,10 +81,12 @@ bool async_ok(const GemmDesc& d) {
          aligned16(d.aux) && aligned16(d.residual) && aligned16(d.bias) && phases_ok(d, 8);
 }
 
-// Extent in bytes of a row-major operand of `rows` rows of `cols` elements at
-// stride `ld`.
-int64_t extent_bytes(int64_t rows, int64_t cols, int64_t ld, int64_t es) {
-  return ((rows - 1) * ld + cols) * es;
+// Extent in bytes of a row-major bf16 operand of `rows` rows of `cols` elements at
+// stride `ld`, in whole dwords: a load drops the dword that crosses a descriptor's end,
+// and with it the last element of the last row where `cols` is odd. (Strides are
+// multiples of 8, so an odd row is followed by its own padding.)
+int64_t extent_bytes(int64_t rows, int64_t cols, int64_t ld) {
+  return ((rows - 1) * ld + cols + (cols & 1)) * 2;
 }
 
 // Operand rows and columns of a product (A is M x K or K x M, B is N x K or K x N).
@@ -519,14 +521,14 @@ gemm::Params make_params(const GemmDesc& d, const GemmPlan& pl) {
   // only where xl_ok holds; launch_gemm refuses them otherwise).
   p.a2_bytes = 0;
   if (buffer_loads(d, pl) && two_phase(d)) {  // k-slices of a two-phase forward product
-    p.a_bytes = static_cast<uint32_t>(extent_bytes(d.M, d.K1, d.lda, 2));
-    p.a2_bytes = static_cast<uint32_t>(extent_bytes(d.M, d.K - d.K1, d.lda2, 2));
-    p.b_bytes = static_cast<uint32_t>(extent_bytes(d.K, d.N, d.ldb, 2));
+    p.a_bytes = static_cast<uint32_t>(extent_bytes(d.M, d.K1, d.lda));
+    p.a2_bytes = static_cast<uint32_t>(extent_bytes(d.M, d.K - d.K1, d.lda2));
+    p.b_bytes = static_cast<uint32_t>(extent_bytes(d.K, d.N, d.ldb));
   } else if (buffer_loads(d, pl)) {
     int64_t ar, ac, br, bc;
     operand_dims(d, ar, ac, br, bc);
-    p.a_bytes = static_cast<uint32_t>(extent_bytes(ar, ac, d.lda, 2));
-    p.b_bytes = static_cast<uint32_t>(extent_bytes(br, bc, d.ldb, 2));
+    p.a_bytes = static_cast<uint32_t>(extent_bytes(ar, ac, d.lda));
+    p.b_bytes = static_cast<uint32_t>(extent_bytes(br, bc, d.ldb));
   } else {
     p.a_bytes = p.b_bytes = 0;
   }

@@ -137,3 +137,31 @@ def test_async_model_gradient(cfg):
     for l, ((gw, gb), (rw, rb)) in enumerate(zip(m.unpack(dP), rg)):
         assert_close(to_np(gw), rw, TOL["bf16"], ("dW", l))
         assert_close(to_np(gb), rb, TOL["bf16"], ("db", l))
+
+
+@pytest.mark.parametrize("classes", [33, 130, 257, 481])
+@pytest.mark.parametrize("batch,K", [(300, 232), (9, 8), (520, 1000)])
+@pytest.mark.parametrize("forced", [10, 11, 12, 13, 16, 17, 18, 19])
+def test_output_layer_of_any_width(forced, batch, K, classes, monkeypatch):
+    """Logits [batch, classes] have rows that start anywhere, and W's padded rows end at
+    `classes`: an odd count ends inside a dword, which loads through a descriptor that
+    stopped there would drop from the last row of W. Elementwise, any order of a float32
+    sum of K products is within K 2^-24 of the terms' magnitudes (8 more roundings for
+    the bias); a lost term is 1 / K of them."""
+    import torch
+    monkeypatch.setenv("DLVM_GEMM_CONFIG", str(forced))
+    r = _rng(14, batch, K, classes)
+    x = r.standard_normal((batch, K)).astype(np.float32)
+    W = (r.uniform(0.5, 1.0, (K, classes)) * r.choice([-1, 1], (K, classes))).astype(np.float32)
+    b = r.uniform(-0.5, 0.5, classes).astype(np.float32)
+    m = dl.Model((K, classes), ("none",), "bf16", "softmax_ce", False, batch)
+    assert re.search(rf"gemm_nn_bf16_\d+x\d+c{forced}(s\d+)?$", m.plan(batch)[0]["name"]), m.plan(batch)[0]
+    P = m.pack([(W, b)], device(), torch.bfloat16)
+    ws = torch.full((m.workspace_bytes(batch),), 0xFF, dtype=torch.uint8, device=device())
+    out = torch.full((batch, classes), float("nan"), device=device())
+    m.forward(P, to_dev(x, "bf16"), batch, out, ws)
+    torch.cuda.synchronize()
+    x, W, b = quant(x, "bf16"), quant(W, "bf16"), quant(b, "bf16")
+    off = np.abs(to_np(out) - (x @ W + b))
+    lim = (K + 8) * 2.0 ** -24 * (np.abs(x) @ np.abs(W) + np.abs(b))
+    assert (off <= lim).all(), float((off / lim).max())
