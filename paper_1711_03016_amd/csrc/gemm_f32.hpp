@@ -139,6 +139,15 @@ __device__ __forceinline__ void f32_frag(float (&f)[4], const char* lds, int row
   }
 }
 
+// Accumulators per output: instruction e of a step adds to accumulator e % ACC, and they
+// are summed in pairs before the epilogue. A float32 sum's error grows with the root of
+// its length (1000 terms: 5.7e-7 of the norm on one accumulator, 3.9e-7 on two, 2.8e-7 on
+// four), and the tiles of few blocks have the registers for more than one. (The
+// instructions of a wave with one block no longer wait for each other, which with two
+// workgroups on a compute unit gains nothing: 2049 x 1001 x 777, all three products, 126 us
+// either way.)
+template <int TM, int TN> constexpr int f32_accs() { return TM * TN >= 4 ? 1 : 4 / (TM * TN); }
+
 // One step (8 k) of the wave's TM x TN blocks: the matrix instructions of the
 // fragments in register set CUR, with the reads of step s2 of the k-tile at
 // (As2, Bs2) into the other set ahead of them. Consecutive instructions go to
@@ -147,7 +156,9 @@ template <bool AK, bool BKM, int BM, int BN, int TM, int TN, bool CS, int CUR>
 __device__ __forceinline__ void f32_step(float (&a)[2][TM][4], float (&b)[2][TN][4],
                                          const char* __restrict__ As2, const char* __restrict__ Bs2,
                                          int s2, int arow, int brow, int lane,
-                                         f32x16 (&acc)[TM][TN], float (&cs)[TN], bool do_cs) {
+                                         f32x16 (&acc)[f32_accs<TM, TN>()][TM][TN],
+                                         float (&cs)[TN], bool do_cs) {
+  constexpr int ACC = f32_accs<TM, TN>();
 #pragma unroll
   for (int i = 0; i < TM; ++i) f32_frag<AK, BM>(a[CUR ^ 1][i], As2, arow + 32 * i, s2, lane);
 #pragma unroll
@@ -158,8 +169,9 @@ __device__ __forceinline__ void f32_step(float (&a)[2][TM][4], float (&b)[2][TN]
     for (int i = 0; i < TM; ++i)
 #pragma unroll
       for (int j = 0; j < TN; ++j)
-        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[CUR][i][e], b[CUR][j][e], acc[i][j], 0, 0, 0);
-  // One instruction per accumulator first: the set the reads go to feeds the
+        acc[e % ACC][i][j] =
+            __builtin_amdgcn_mfma_f32_32x32x2f32(a[CUR][i][e], b[CUR][j][e], acc[e % ACC][i][j], 0, 0, 0);
+  // One instruction per block first: the set the reads go to feeds the
   // previous step's last instructions, which are then done with it. Then the
   // reads between the others (two per instruction).
   __builtin_amdgcn_sched_group_barrier(0x008, TM * TN, 0);
@@ -233,13 +245,16 @@ __device__ __forceinline__ void f32_gemm_tile(const Params& p, const int tile, c
     }
   };
 
-  f32x16 acc[TM][TN];
+  constexpr int ACC = f32_accs<TM, TN>();
+  f32x16 accs[ACC][TM][TN];
 #pragma unroll
-  for (int i = 0; i < TM; ++i)
+  for (int q = 0; q < ACC; ++q)
 #pragma unroll
-    for (int j = 0; j < TN; ++j)
+    for (int i = 0; i < TM; ++i)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.0f;
+      for (int j = 0; j < TN; ++j)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) accs[q][i][j][r] = 0.0f;
   float cs[TN];
 #pragma unroll
   for (int j = 0; j < TN; ++j) cs[j] = 0.0f;
@@ -276,9 +291,9 @@ __device__ __forceinline__ void f32_gemm_tile(const Params& p, const int tile, c
   for (int kt = 0; kt < nk; ++kt) {
     const char* As = smem + (kt % STAGES) * STAGE;
     const char* Bs = As + A_BYTES;
-    f32_step<AK, BKM, BM, BN, TM, TN, DW, 0>(a, b, As, Bs, 1, arow, brow, lane, acc, cs, do_colsum);
-    f32_step<AK, BKM, BM, BN, TM, TN, DW, 1>(a, b, As, Bs, 2, arow, brow, lane, acc, cs, do_colsum);
-    f32_step<AK, BKM, BM, BN, TM, TN, DW, 0>(a, b, As, Bs, 3, arow, brow, lane, acc, cs, do_colsum);
+    f32_step<AK, BKM, BM, BN, TM, TN, DW, 0>(a, b, As, Bs, 1, arow, brow, lane, accs, cs, do_colsum);
+    f32_step<AK, BKM, BM, BN, TM, TN, DW, 1>(a, b, As, Bs, 2, arow, brow, lane, accs, cs, do_colsum);
+    f32_step<AK, BKM, BM, BN, TM, TN, DW, 0>(a, b, As, Bs, 3, arow, brow, lane, accs, cs, do_colsum);
     __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0): the last step's fragments
     const bool more = kt + 1 < nk;
     if (more) {
@@ -290,9 +305,19 @@ __device__ __forceinline__ void f32_gemm_tile(const Params& p, const int tile, c
     if (more) zero_tail(kt + 1);
     // (after the last k-tile these reads of another slot are not used)
     const char* An = smem + ((kt + 1) % STAGES) * STAGE;
-    f32_step<AK, BKM, BM, BN, TM, TN, DW, 1>(a, b, An, An + A_BYTES, 0, arow, brow, lane, acc, cs,
+    f32_step<AK, BKM, BM, BN, TM, TN, DW, 1>(a, b, An, An + A_BYTES, 0, arow, brow, lane, accs, cs,
                                              do_colsum);
   }
+
+#pragma unroll
+  for (int w = ACC / 2; w >= 1; w /= 2)
+#pragma unroll
+    for (int q = 0; q < w; ++q)
+#pragma unroll
+      for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j) accs[q][i][j] += accs[q + w][i][j];
+  const f32x16 (&acc)[TM][TN] = accs[0];
 
   if constexpr (EPI == EPI_CHAIN) {
     // (one loss partial per wavefront, as the register-staged kernel's epilogue)

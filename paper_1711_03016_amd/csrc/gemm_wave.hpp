@@ -356,7 +356,8 @@ __device__ __forceinline__ void wave_gemm_body(const Params& p, int64_t m0, int6
   }
 
   // Steps: the whole ones of both phases in order, shared out over the waves;
-  // what is left of phase 1 goes to the first wave, of phase 2 to the last.
+  // what is left goes to the first wave, which never has more steps than another (of
+  // two phases: what is left of the second to the last wave).
   const int64_t K1 = PH2 ? p.K1 : p.K;
   const int nf1 = static_cast<int>(K1 / STEP);
   const int nf = PH2 ? nf1 + static_cast<int>((p.K - K1) / STEP) : nf1;
@@ -391,11 +392,20 @@ __device__ __forceinline__ void wave_gemm_body(const Params& p, int64_t m0, int6
   if constexpr (PH2) oa2.init(p.lda2, lane, p.M - m0);
   ob.init(p.ldb, lane, p.N - n0);
 
-  f32x4 acc[AB][BB];
+  // float32: instruction e of a step adds to accumulator e % ACC, summed in pairs at the
+  // end. These tiles take products that larger tiles would split over k, so four sums per
+  // wave keep a sum as short as theirs (1000 terms: 1.1e-7 of the norm, 2.1e-7 with one
+  // per wave). Larger tiles have no registers for it (136 on 2 x 2 blocks: one workgroup
+  // per compute unit), and the steps of a recurrence, one after the other, are better
+  // without the additions (48 launches 137 us, 139 with them; their sums are short).
+  constexpr int ACC = sizeof(T) == 4 && AB * BB <= 2 && !PH2 ? 4 : 1;
+  f32x4 accs[ACC][AB][BB];
 #pragma unroll
-  for (int i = 0; i < AB; ++i)
+  for (int q = 0; q < ACC; ++q)
 #pragma unroll
-    for (int j = 0; j < BB; ++j) acc[i][j] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+    for (int i = 0; i < AB; ++i)
+#pragma unroll
+      for (int j = 0; j < BB; ++j) accs[q][i][j] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
   float cs[BB];
 #pragma unroll
   for (int j = 0; j < BB; ++j) cs[j] = 0.0f;
@@ -425,7 +435,8 @@ __device__ __forceinline__ void wave_gemm_body(const Params& p, int64_t m0, int6
         for (int i = 0; i < AB; ++i)
 #pragma unroll
           for (int j = 0; j < BB; ++j)
-            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(ra.v[e][i], rb.v[e][j], acc[i][j], 0, 0, 0);
+            accs[e % ACC][i][j] =
+                __builtin_amdgcn_mfma_f32_16x16x4f32(ra.v[e][i], rb.v[e][j], accs[e % ACC][i][j], 0, 0, 0);
       if constexpr (EPI == EPI_DW) {
         if (do_colsum) {
 #pragma unroll
@@ -442,7 +453,7 @@ __device__ __forceinline__ void wave_gemm_body(const Params& p, int64_t m0, int6
       for (int i = 0; i < AB; ++i)
 #pragma unroll
         for (int j = 0; j < BB; ++j)
-          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[i], fb[j], acc[i][j], 0, 0, 0);
+          accs[0][i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[i], fb[j], accs[0][i][j], 0, 0, 0);
       if constexpr (EPI == EPI_DW) {
         if (do_colsum) {
 #pragma unroll
@@ -467,7 +478,7 @@ __device__ __forceinline__ void wave_gemm_body(const Params& p, int64_t m0, int6
 
   // A partial step (fewer k left of a phase than a step has), its loads first of all.
   const bool t1 = PH2 && tail1 > 0 && wave == 0;
-  const bool t2 = tail2 > 0 && wave == NW - 1;
+  const bool t2 = tail2 > 0 && wave == (PH2 ? NW - 1 : 0);
   typename OA::Regs ta;
   typename OB::Regs tb;
   if (t1 || t2) {
@@ -500,6 +511,16 @@ __device__ __forceinline__ void wave_gemm_body(const Params& p, int64_t m0, int6
       if (s + d < s1) multiply(d);
   }
   if (t1 || t2) products(ta, tb);
+
+#pragma unroll
+  for (int h = ACC / 2; h >= 1; h /= 2)
+#pragma unroll
+    for (int q = 0; q < h; ++q)
+#pragma unroll
+      for (int i = 0; i < AB; ++i)
+#pragma unroll
+        for (int j = 0; j < BB; ++j) accs[q][i][j] += accs[q + h][i][j];
+  const f32x4 (&acc)[AB][BB] = accs[0];
 
   // Partial tiles to LDS in row-major order. Accumulator register r of block
   // (i, j) holds the block's row 4 g + r and column l.

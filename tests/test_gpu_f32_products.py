@@ -66,6 +66,48 @@ def test_layer(cfg, shape):
     _layer(*shape)
 
 
+def _error_of_sums(a, b, parts):
+    """Relative error of the dot products of a's rows with b's rows when each is `parts`
+    float32 sums, one after the other, that are then added up in pairs."""
+    n, K = a.shape
+    k = np.concatenate([np.arange(K), np.full(-K % parts, -1)]).reshape(-1, parts)
+    acc = np.zeros((n, parts), np.float32)
+    for q in k:
+        t = a[:, q].astype(np.float64) * b[:, q].astype(np.float64) * (q >= 0)
+        acc = (acc + t).astype(np.float32)
+    while acc.shape[1] > 1:
+        acc = acc[:, ::2] + acc[:, 1::2]
+    ref = (a.astype(np.float64) * b).sum(1)
+    return np.linalg.norm(acc[:, 0] - ref) / np.linalg.norm(ref)
+
+
+# Sums that each configuration keeps of one output: its waves or k-groups times its
+# accumulators (one network's products may run on any of them, so a longer sum is an error
+# that grows from one size to the next).
+SUMS = {6: 32, 7: 32, 8: 8, 9: 4, 20: 1, 21: 4, 22: 2, 23: 8}
+
+
+def test_sums_are_kept_in_parts(cfg):
+    """The error of all three products against float64 is that of sums in as many parts as
+    the configuration keeps (15% for the sample and for what the order of the parts adds;
+    half as many parts are 1.41 times as far off)."""
+    import torch
+    M = N = K = 1000
+    r = np.random.default_rng(34)
+    X, W, dY = (r.standard_normal((1000, 1000)).astype(np.float32) for _ in range(3))
+    H, dX, dW = (torch.empty((1000, 1000), device=device()) for _ in range(3))
+    dl.dense_forward("f32", "f32", "none", M, N, K, 1.0, to_dev(X), to_dev(W), None, H)
+    dl.dense_backward_data("f32", "f32", "none", M, N, K, to_dev(dY), to_dev(W), None, None, dX)
+    dl.dense_backward_params("f32", M, N, K, to_dev(X), to_dev(dY), dW, None)
+    torch.cuda.synchronize()
+    want = _error_of_sums(r.standard_normal((4000, 1000)).astype(np.float32),
+                          r.standard_normal((4000, 1000)).astype(np.float32), SUMS[cfg])
+    X, W, dY = (a.astype(np.float64) for a in (X, W, dY))
+    for got, ref, what in ((H, X @ W, "NN"), (dX, dY @ W.T, "NT"), (dW, X.T @ dY, "TN")):
+        off = np.linalg.norm(to_np(got) - ref) / np.linalg.norm(ref)
+        assert off <= 1.15 * want, (what, off, want)
+
+
 @pytest.mark.parametrize("shape", [(3, (1 << 22) + 24, 5), (2, 9, (1 << 22) + 4)])
 def test_far_leading_dimensions(shape):
     """Rows of more than 2^22 elements: the byte offsets of a step would pass 2^31."""
