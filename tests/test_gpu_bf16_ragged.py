@@ -18,9 +18,10 @@ pytestmark = pytest.mark.gpu
 
 CFGS = [0, 1, 2, 3, 4, 5, 6, 7, 8, 9, 23]
 # (M, N, K): one element, rows shorter than a chunk, exactly one, one more; odd sizes past
-# one tile of each configuration; sizes that aligned loads take; many steps
+# one tile of each configuration; sizes that aligned loads take; many steps; two and three
+# columns past a tile of 64
 SHAPES = [(1, 1, 1), (3, 5, 7), (9, 8, 9), (33, 17, 70), (129, 65, 131), (70, 257, 63), (64, 96, 256),
-          (200, 34, 1027)]
+          (200, 34, 1027), (30, 67, 66), (30, 66, 67)]
 
 
 @pytest.fixture(params=CFGS)

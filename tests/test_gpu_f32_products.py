@@ -19,9 +19,10 @@ pytestmark = pytest.mark.gpu
 
 CFGS = [6, 7, 8, 9, 20, 21, 22, 23]
 # (M, N, K): smaller than one step and one tile, exact tiles, one past a tile in every
-# size, sizes that no vector load divides, fewer steps than waves, many k-tiles
+# size, sizes that no vector load divides, fewer steps than waves, many k-tiles, two and
+# three columns past a tile of 64
 SHAPES = [(1, 1, 1), (5, 3, 7), (128, 128, 32), (129, 65, 33), (17, 33, 130), (64, 130, 64),
-          (67, 259, 96), (250, 77, 515), (33, 18, 2056)]
+          (67, 259, 96), (250, 77, 515), (33, 18, 2056), (30, 67, 66), (30, 66, 67)]
 
 
 def _near(got, ref, magnitude, K, what):
