@@ -146,9 +146,7 @@ WsLayout ws_layout(const dlvm_model* m, int64_t B) {
   off = align_up(off + 16);
   int64_t np = std::max<int64_t>(dlvm::softmax_xent_partials(B),
                                  dlvm::chain8_partials(B, m->widths[m->L]));
-  // the chain epilogue writes one partial per wavefront of at least a 32 x 32 block,
-  // or one per tile of at least 16 x 16
-  if (m->chain_epi) np = std::max<int64_t>(np, (B + 15) / 16 * ((m->widths[m->L] + 15) / 16));
+  if (m->chain_epi) np = std::max<int64_t>(np, dlvm::chain_partials_bound(B, m->widths[m->L]));
   w.partials = off;
   off = align_up(off + static_cast<size_t>(np) * 4);
   w.bad = off;

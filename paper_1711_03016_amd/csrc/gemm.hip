@@ -128,6 +128,9 @@ bool wave_ok(const GemmDesc& d) {
          (!two_phase(d) || d.lda2 <= lim);
 }
 
+// Loss partials a tile of the chain epilogue writes.
+int chain_waves(int cfg) { return wave_config(cfg) ? 1 : 4; }  // (20-22: 2 x 2 waves)
+
 // The float32 kernel with direct-to-LDS loads (configurations 20-22): any size
 // and alignment; the byte offsets inside a k-tile stay below 2^31.
 bool f32_config(int cfg) { return cfg >= 20 && cfg <= 22; }
@@ -426,8 +429,15 @@ GemmPlan chosen(const GemmDesc& d, bool assume_aligned, int64_t capacity, int fo
 }  // namespace
 
 int64_t chain_partials(const GemmPlan& pl) {
-  const int waves = wave_config(pl.cfg) ? 1 : 4;  // (configurations 20-22: 2 x 2 waves)
-  return static_cast<int64_t>(pl.tiles_m) * pl.tiles_n * waves;
+  return static_cast<int64_t>(pl.tiles_m) * pl.tiles_n * chain_waves(pl.cfg);
+}
+
+int64_t chain_partials_bound(int64_t M, int64_t N) {
+  int64_t most = 0;
+  for (const TileShape& t : kTiles)
+    if (wave_config(t.cfg) || f32_config(t.cfg))
+      most = std::max<int64_t>(most, ceil_div(M, t.bm) * ceil_div(N, t.bn) * chain_waves(t.cfg));
+  return most;
 }
 
 GemmPlan plan_gemm(const GemmDesc& d) {

@@ -17,6 +17,7 @@ hipError_t launch_nn(const Params& p, int dtype, int out_dtype, int cfg, unsigne
       return launch_vec<bf16_t, float, true, false, EPI_STORE, true>(p, cfg, grid, va, vb, s);
     return launch_vec<bf16_t, bf16_t, true, false, EPI_STORE, true>(p, cfg, grid, va, vb, s);
   }
+  if (p.partials != nullptr) return hipErrorInvalidValue;  // (the chain runs on 6-9 and 20-23)
   if (dtype == F32) {  // (16-byte loads of both operands, or element loads of both: the same sums)
     if (va && vb) return launch_cfg<float, float, true, false, true, true, EPI_STORE>(p, cfg, grid, s);
     return launch_cfg<float, float, true, false, false, false, EPI_STORE>(p, cfg, grid, s);

@@ -123,6 +123,9 @@ void tuning_scope_end();
 // Loss partials a chain-epilogue product writes (one per wavefront of a tile, or
 // one per tile where the waves share the contraction).
 int64_t chain_partials(const GemmPlan& plan);
+// The most of them over every configuration that an M x N product may be planned on
+// (a 64 x 64 tile of four waves writes four, however little of it the output fills).
+int64_t chain_partials_bound(int64_t M, int64_t N);
 
 // Enqueue one GEMM with its fused epilogue as planned. Returns hipSuccess or
 // the launch error. The caller has validated shapes and pointers.

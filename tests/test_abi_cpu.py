@@ -425,6 +425,23 @@ def test_small_network_plan(monkeypatch):
     assert small.plan(16)[0]["name"].startswith("gemm_nn")
 
 
+@pytest.mark.parametrize("cfg", [6, 7, 8, 9, 20, 21, 22, 23])
+def test_chain_epilogue_partials_fit_their_region(cfg, monkeypatch):
+    """The loss partials that the chain epilogue writes (the size of the plan's
+    finalisation) are at most those the workspace is laid out for, on every tile: four
+    waves of a 64 x 64 tile write one each however little of it the output fills."""
+    monkeypatch.setenv("DLVM_GEMM_CONFIG", str(cfg))
+    bound = dl.lib()._ZN4dlvm20chain_partials_boundEll
+    bound.restype, bound.argtypes = ctypes.c_int64, [ctypes.c_int64, ctypes.c_int64]
+    for batch in (1, 16, 17, 64, 65, 129):
+        for n in (1, 15, 16, 17, 64, 65, 129, 1025):
+            plan = dl.Model((n, n), ("none",), "f32", "chain8", True, batch, chain_in_epilogue=True).plan(batch)
+            assert plan[0]["name"].startswith("gemm_nn_chain8_f32_") and plan[0]["name"].endswith(f"c{cfg}")
+            written = [p["M"] for p in plan if p["name"] == "finalize"]
+            assert len(written) == 1 and 0 < written[0] <= bound(batch, n), (batch, n, written)
+    assert bound(1, 65) >= 8 > -(-1 // 16) * -(-65 // 16)  # (two 64 x 64 tiles of four waves)
+
+
 def test_one_hip_runtime_whatever_the_import_order():
     """The library loaded before the caller imports torch still binds to
     torch's HIP runtime: one libamdhip64 mapped in the process (a second one
