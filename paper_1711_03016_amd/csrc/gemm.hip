@@ -98,9 +98,10 @@ void operand_dims(const GemmDesc& d, int64_t& ar, int64_t& ac, int64_t& br, int6
 
 // The buffer-descriptor kernel addresses its operands with 32-bit byte
 // offsets: every offset it forms (up to one tile past either extent) must stay
-// below 2^31.
-bool xl_ok(const GemmDesc& d) {
-  if (!async_ok(d) || two_phase(d)) return false;
+// below 2^31. `assume_aligned` leaves the addresses out (for sizing scratch before they
+// exist).
+bool xl_ok(const GemmDesc& d, bool assume_aligned = false) {
+  if (!(assume_aligned ? async_strides_ok(d) : async_ok(d)) || two_phase(d)) return false;
   int64_t ar, ac, br, bc;
   operand_dims(d, ar, ac, br, bc);
   const int64_t lim = int64_t(1) << 31;
@@ -309,10 +310,10 @@ GemmPlan choose(const GemmDesc& d, bool assume_aligned, int64_t capacity, int fo
     // register-staged 64 x 64 and 128 x 128 tiles are never faster (with one
     // workgroup per compute unit they cannot hide their load latency).
     if (can_async && (t.cfg == 0 || t.cfg == 1 || t.cfg == 4) && forced != t.cfg) continue;
-    if ((t.cfg == 14 || t.cfg == 15) && (!xl_ok(d) || d.ldc % 8 != 0)) continue;  // (16-byte stores)
+    if ((t.cfg == 14 || t.cfg == 15) && (!xl_ok(d, assume_aligned) || d.ldc % 8 != 0)) continue;  // (16-byte stores)
     // The direct-to-LDS tiles load one-phase products through buffer
     // descriptors: operand extents below 2^31 bytes.
-    if (t.async && !two_phase(d) && !xl_ok(d)) continue;
+    if (t.async && !two_phase(d) && !xl_ok(d, assume_aligned)) continue;
     // Measured on 16384 x 4096 x 4096: the four-wave kernel is the faster
     // one for the forward layout only; 15 runs only when forced.
     if (t.cfg == 14 && d.layout != Layout::NN && forced != 14) continue;

@@ -442,6 +442,42 @@ def test_chain_epilogue_partials_fit_their_region(cfg, monkeypatch):
     assert bound(1, 65) >= 8 > -(-1 // 16) * -(-65 // 16)  # (two 64 x 64 tiles of four waves)
 
 
+_SCRATCH_SIZES = r"""
+#include <cstdio>
+#include "kernels.hpp"
+int main(int argc, char**) {  // any argument: the misaligned operand is asked about first
+  dlvm::GemmDesc d{};
+  d.layout = dlvm::Layout::TN;
+  d.dtype = 1;
+  d.M = d.lda = 1024;
+  d.N = d.ldb = d.ldc = d.nvec = 1024;
+  d.K = 4096;
+  const dlvm::GemmDesc none = d;
+  d.A = reinterpret_cast<const void*>(0x10002);
+  const long a = dlvm::split_ws_elems(argc > 1 ? d : none), b = dlvm::split_ws_elems(argc > 1 ? none : d);
+  std::printf("%ld %ld\n", a, b);
+}
+"""
+
+
+def test_scratch_sizes_do_not_depend_on_addresses(tmp_path):
+    """Scratch is sized before the operands exist, so their addresses must not count, nor
+    which of two products of the same sizes was planned first."""
+    import subprocess
+    from paper_1711_03016_amd import build
+    src, exe = tmp_path / "sizes.cpp", tmp_path / "sizes"
+    src.write_text(_SCRATCH_SIZES)
+    root = os.path.dirname(dl.LIB_PATH)
+    cc = [build.HIPCC, "-std=c++17", "-O1", f"-I{root}/csrc", f"-I{os.path.dirname(root)}/include", str(src),
+          f"-L{root}", "-l:libdlvm.so", f"-Wl,-rpath,{root}", "-o", str(exe)]
+    subprocess.run(cc, check=True, capture_output=True, timeout=300)
+    got = {subprocess.run([str(exe), *a], check=True, capture_output=True, text=True, timeout=300).stdout
+           for a in ([], ["first"])}
+    assert len(got) == 1, got
+    a, b = map(int, got.pop().split())
+    assert a == b > 0
+
+
 def test_one_hip_runtime_whatever_the_import_order():
     """The library loaded before the caller imports torch still binds to
     torch's HIP runtime: one libamdhip64 mapped in the process (a second one
