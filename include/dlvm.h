@@ -140,8 +140,9 @@ size_t dlvm_workspace_bytes(const dlvm_model* m, int64_t batch);
  *     shares a slot with other layers and holds whatever was computed there last.
  *   DLVM_WS_LOGITS (layer ignored): the output layer's product, float32
  *     [batch, widths[L]] (the logits; z = x.W for CHAIN8). DLVM_ERR_UNSUPPORTED
- *     when the plan never stores it: a softmax head whose product the loss
- *     kernel receives as k-slices, or a chain run in the product's epilogue.
+ *     when the plan never stores it: a softmax head of at most 256 classes in a
+ *     batch small enough that its loss is taken from parts of the contraction,
+ *     or a chain run in the product's epilogue.
  *   DLVM_WS_ADJOINT, layer l in [1, L]: dZ_l, the adjoint of layer l's output
  *     before its activation (l = L: the adjoint of the logits, (softmax(z) -
  *     onehot(y)) / batch for SOFTMAX_CE), ld = the row stride of W_l

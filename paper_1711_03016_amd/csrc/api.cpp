@@ -122,11 +122,34 @@ GemmDesc gemm_nn(int dtype, int out_dtype, int act, int64_t M, int64_t N, int64_
                  const void* X, const void* W, int64_t ldw, const void* bias, void* H,
                  int64_t ldh);
 
-// k-slices of the output layer's product in a gradient call (1: none). A
-// softmax head with few classes has few output tiles per batch; its
-// contraction is split so that more workgroups share it, and the slices are
-// summed (with the bias) by the softmax cross-entropy kernel that follows.
-int head_splits(const dlvm_model* m, int64_t B) {
+// Address arithmetic on integers: a dry run (plan description) uses null bases.
+template <typename T> T* at(const void* base, size_t off) {
+  return reinterpret_cast<T*>(reinterpret_cast<uintptr_t>(base) + off);
+}
+
+const void* param_ptr(const dlvm_model* m, const void* params, int64_t elem_off) {
+  return at<const void>(params, static_cast<size_t>(elem_off) * elem_size(m->dtype));
+}
+
+// The output layer's product in a gradient call, from h (H_{L-1}) to `logits`.
+GemmDesc head_desc(const dlvm_model* m, const void* params, const void* h, int64_t B, void* logits) {
+  const int L = m->L;
+  return gemm_nn(m->dtype, DLVM_F32, DLVM_ACT_NONE, B, m->widths[L], m->widths[L - 1], 1.0f, h,
+                 param_ptr(m, params, m->offsets[2 * (L - 1)]), m->ldw[L - 1],
+                 param_ptr(m, params, m->offsets[2 * L - 1]), logits, m->widths[L]);
+}
+
+// Whether the product and its softmax cross-entropy share a launch (few classes).
+bool head_fused(const dlvm_model* m, int64_t B) {
+  return m->loss == DLVM_LOSS_SOFTMAX_CE &&
+         dlvm::head_xent_ok(head_desc(m, nullptr, nullptr, B, nullptr), m->ldw[m->L - 1]);
+}
+
+// Parts that share the contraction of the output layer (1: one). A softmax head of at most
+// 256 classes has few output tiles in a small batch, so more workgroups or waves share its
+// contraction than its tiles would give it, and the loss is taken from the parts: its
+// logits are then not stored.
+int head_parts(const dlvm_model* m, int64_t B) {
   if (m->loss != DLVM_LOSS_SOFTMAX_CE) return 1;
   const int64_t C = m->widths[m->L], K = m->widths[m->L - 1];
   if (C > 256 || K < 128) return 1;
@@ -135,6 +158,10 @@ int head_splits(const dlvm_model* m, int64_t B) {
   while (s < 8 && K / (2 * s) >= 64 && tiles * 2 * s <= 256) s *= 2;
   return s;
 }
+
+// k-slices of a head that has a launch of its own, summed (with the bias) by the softmax
+// cross-entropy kernel that follows. A fused head's waves add theirs in LDS.
+int head_splits(const dlvm_model* m, int64_t B) { return head_fused(m, B) ? 1 : head_parts(m, B); }
 
 bool relu_mask_planned(const dlvm_model* m, const void* params, const void* x, int64_t batch,
                        void* ws, const WsLayout& w, int l);
@@ -211,15 +238,6 @@ WsLayout ws_layout(const dlvm_model* m, int64_t B) {
   }
   w.total = off;
   return w;
-}
-
-// Address arithmetic on integers: a dry run (plan description) uses null bases.
-template <typename T> T* at(const void* base, size_t off) {
-  return reinterpret_cast<T*>(reinterpret_cast<uintptr_t>(base) + off);
-}
-
-const void* param_ptr(const dlvm_model* m, const void* params, int64_t elem_off) {
-  return at<const void>(params, static_cast<size_t>(elem_off) * elem_size(m->dtype));
 }
 
 dlvm_status check_batch(const dlvm_model* m, int64_t batch) {
@@ -712,32 +730,32 @@ dlvm_status plan_gradient(const dlvm_model* m, const void* params, const void* x
   np = dlvm::softmax_xent_partials(batch);
   // Output layer: logits, then softmax cross-entropy and its adjoint. A split
   // product leaves its k-slices in the scratch; the loss kernel sums them.
-  GemmDesc head = gemm_nn(dt, DLVM_F32, DLVM_ACT_NONE, batch, C, m->widths[L - 1], 1.0f, h,
-                          P(2 * (L - 1)), m->ldw[L - 1], P(2 * L - 1), at<void>(ws, w.logits), C);
-  head.split_ws = at<float>(ws, w.splitk);
-  head.split_ws_elems = w.splitk_elems;
-  const int hs = head_splits(m, batch);
+  GemmDesc head = head_desc(m, params, h, batch, at<void>(ws, w.logits));
   void* const dzL = at<void>(ws, w.dz[L - 1]);
-  if (dlvm::head_xent_ok(head, ldc)) {
-    // (few classes: product and loss share a launch, whose waves split the
-    // contraction; the logits are stored where dlvm_workspace_tensor promises them)
-    if (hs > 1) head.C = nullptr;
+  if (head_fused(m, batch)) {
+    // (few classes: product and loss share a launch; the logits are stored where
+    // dlvm_workspace_tensor promises them)
+    const bool kept = head_parts(m, batch) <= 1;
+    if (!kept) head.C = nullptr;
+    np = dlvm::head_xent_partials(batch);
     st = run.run(
         [&] {
           LaunchInfo info = gemm_info(head);
-          info.name = hs > 1 ? std::string("split_softmax_xent") : info.name + "_softmax_xent";
-          info.bytes += double(batch) * C * ((hs > 1 ? -4.0 : 0.0) + es) + 4.0 * batch;
+          info.name = kept ? info.name + "_softmax_xent" : std::string("head_softmax_xent");
+          info.bytes += double(batch) * C * ((kept ? 0.0 : -4.0) + es) + 4.0 * batch;
           return info;
         },
         [&](hipStream_t s) {
-          return dlvm::launch_head_xent(head, labels, scale, dzL, ldc, partials, bad, &np, s);
+          return dlvm::launch_head_xent(head, labels, scale, dzL, ldc, partials, bad, s);
         },
         "output layer and loss launch");
     if (st != DLVM_OK) return st;
     if ((st = finalize()) != DLVM_OK) return st;
     return plan_adjoint_layers(m, params, x, batch, dparams, dx, ws, w, run);
   }
-  head.splits_hint = hs;
+  head.split_ws = at<float>(ws, w.splitk);
+  head.split_ws_elems = w.splitk_elems;
+  head.splits_hint = head_splits(m, batch);
   dlvm::GemmPlan hp{};
   if ((st = run.gemm_raw(head, hp)) != DLVM_OK) return st;
   if (hp.splits > 1) {
@@ -1219,10 +1237,10 @@ dlvm_status dlvm_workspace_tensor(const dlvm_model* m, int64_t batch, int32_t ki
       *dtype = m->dtype;
       return DLVM_OK;
     case DLVM_WS_LOGITS:
-      if (chain ? m->chain_epi != 0 : head_splits(m, batch) > 1)
+      if (chain ? m->chain_epi != 0 : head_parts(m, batch) > 1)
         return fail(DLVM_ERR_UNSUPPORTED,
-                    "this plan never stores the output layer's product (its loss kernel sums "
-                    "the product's k-slices, or the chain runs in the product's epilogue)");
+                    "this plan never stores the output layer's product (its loss is taken from "
+                    "parts of the contraction, or the chain runs in the product's epilogue)");
       *offset = w.logits;
       *ld = m->widths[L];
       *dtype = DLVM_F32;

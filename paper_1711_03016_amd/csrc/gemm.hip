@@ -575,15 +575,16 @@ bool head_xent_ok(const GemmDesc& head, int64_t ld_dlogits) {
   return head.layout == Layout::NN && head.N <= 32 && ld_dlogits <= (head.N <= 16 ? 16 : 32) && wave_ok(head);
 }
 
+int head_xent_partials(int64_t rows) { return static_cast<int>(ceil_div(rows, 16)); }
+
 hipError_t launch_head_xent(const GemmDesc& head, const int32_t* labels, float scale, void* dlogits,
-                            int64_t ld_dlogits, float* partials, int32_t* bad, int* n_partials,
-                            hipStream_t s) {
+                            int64_t ld_dlogits, float* partials, int32_t* bad, hipStream_t s) {
   if (!head_xent_ok(head, ld_dlogits)) return hipErrorInvalidValue;
   GemmPlan pl{};
   pl.cfg = head.N <= 16 ? 6 : 7;
   pl.bm = 16;
   pl.bn = head.N <= 16 ? 16 : 32;
-  pl.tiles_m = static_cast<int>(ceil_div(head.M, 16));
+  pl.tiles_m = head_xent_partials(head.M);
   pl.tiles_n = 1;
   pl.splits = 1;
   pl.k_chunk = head.K;
@@ -594,7 +595,6 @@ hipError_t launch_head_xent(const GemmDesc& head, const int32_t* labels, float s
   p.inv_n = scale;
   p.partials = partials;
   p.residual = bad;
-  *n_partials = pl.tiles_m;
   return gemm::launch_wave_xent(p, head.dtype, s);
 }
 

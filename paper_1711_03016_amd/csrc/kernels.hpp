@@ -136,9 +136,9 @@ hipError_t launch_gemm(const GemmDesc& d, const GemmPlan& plan, hipStream_t s);
 // is null), labels, the seed scale and the outputs as launch_softmax_xent, one loss
 // partial and label count per 16 rows.
 bool head_xent_ok(const GemmDesc& head, int64_t ld_dlogits);
+int head_xent_partials(int64_t rows);
 hipError_t launch_head_xent(const GemmDesc& head, const int32_t* labels, float scale, void* dlogits,
-                            int64_t ld_dlogits, float* partials, int32_t* bad, int* n_partials,
-                            hipStream_t s);
+                            int64_t ld_dlogits, float* partials, int32_t* bad, hipStream_t s);
 
 // The two adjoint products of one layer (tn: wrt the weights, nt: wrt the
 // input) can run as one launch when planned on configurations that have a paired kernel.

@@ -155,8 +155,8 @@ def test_workspace_tensors(name):
         assert ld == lds[l - 1]
         assert dt == (dl.F32 if chain else dl.DTYPES[wl.dtype])
         spans.append((off, off + B * ld * (2 if dt == dl.BF16 else 4)))
-    split_head = any(e["name"] == "split_softmax_xent" for e in m.plan(B))
-    if split_head:
+    parts = any(e["name"] in ("split_softmax_xent", "head_softmax_xent") for e in m.plan(B))
+    if parts:
         with pytest.raises(dl.DlvmError) as e:
             m.workspace_tensor_info(B, dl.WS_LOGITS)
         assert e.value.status == dl.ERR_UNSUPPORTED
@@ -476,6 +476,31 @@ def test_scratch_sizes_do_not_depend_on_addresses(tmp_path):
     assert len(got) == 1, got
     a, b = map(int, got.pop().split())
     assert a == b > 0
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("classes,batch", [(10, 256), (32, 100), (10, 9000), (33, 256)])
+def test_head_of_few_classes_in_the_plan(dtype, classes, batch):
+    """A head of at most 32 classes is one launch with its loss: the plan names it so,
+    finalises one loss partial per 16 rows, and no scratch is laid out for k-slices that
+    nobody writes; a wider one is split and keeps its scratch."""
+    K = 2048
+    m = dl.Model((8, K, classes), ("tanh", "none"), dtype, batch_max=batch)
+    plan = m.plan(batch)
+    names = [p["name"] for p in plan]
+    if classes > 32:
+        assert "split_softmax_xent" in names
+        return
+    i = names.index("finalize")
+    assert "split_softmax_xent" not in names and names[i - 1].endswith("softmax_xent")
+    assert plan[i]["M"] == -(-batch // 16)
+    # the workspace ends with the scratch: none but what the other products ask for
+    es = 2 if dtype == "bf16" else 4
+    off, ld, _ = m.workspace_tensor_info(batch, dl.WS_ADJOINT, 2)
+    scratch = m.workspace_bytes(batch) - (off + -(-batch * ld * es // 256) * 256)
+    splits = [p["name"] for p in plan if p["name"].startswith("gemm") and p["name"].split("s")[-1].isdigit()]
+    if not splits:
+        assert scratch == 0, scratch
 
 
 def test_one_hip_runtime_whatever_the_import_order():

@@ -55,7 +55,10 @@ def test_head_loss(dtype, classes, K, batch, monkeypatch):
             assert rel_l2(to_np(gW), rW) <= TOL[dtype] and rel_l2(to_np(gb), rb) <= TOL[dtype]
     else:
         assert (dz == 0).all()
-    kept = not any(e["name"] == "split_softmax_xent" for e in m.plan(batch))
+    fused = classes <= 32
+    names = [e["name"] for e in m.plan(batch)]
+    assert (f"gemm_nn_{dtype}_softmax_xent" in names or "head_softmax_xent" in names) == fused
+    kept = not {"split_softmax_xent", "head_softmax_xent"} & set(names)
     if kept:
         assert_close(to_np(m.workspace_tensor(ws, batch, dl.WS_LOGITS)), logits, TOL[dtype], "logits")
     else:

@@ -214,8 +214,8 @@ def test_loss_adjoint_labels_are_exact(name):
     """The adjoint of the logits that a full-batch gradient call stores in its
     workspace, (softmax - onehot(y)) / B, read back through
     dlvm_workspace_tensor. The heads of c2 (float32) and c3 (bf16) have ten
-    classes: their product is split over k and the loss kernel sums its
-    slices, so this checks that kernel's label handling bit for bit: every
+    classes: product and loss share a launch whose waves split the contraction,
+    so this checks that kernel's label handling bit for bit: every
     row has exactly one negative entry, at its label, and the padding columns
     (10 -> 16) are zero. The values match the oracle's adjoint of its own
     logits."""
@@ -223,8 +223,8 @@ def test_loss_adjoint_labels_are_exact(name):
     x, params, y = workloads.make_inputs(wl, bias_scale=0.1)
     got = _run(wl, x, params, y, forward=False)
     m, ws, B, C = got["model"], got["ws"], wl.batch, wl.widths[-1]
-    assert any(e["name"] == "split_softmax_xent" for e in m.plan(B))
-    with pytest.raises(dl.DlvmError):          # the split head never stores its logits
+    assert any(e["name"] == "head_softmax_xent" for e in m.plan(B))
+    with pytest.raises(dl.DlvmError):          # this head never stores its logits
         m.workspace_tensor(ws, B, dl.WS_LOGITS)
     dz = to_np(m.workspace_tensor(ws, B, dl.WS_ADJOINT, m.n_layers))
     assert dz.shape == (B, 16)
