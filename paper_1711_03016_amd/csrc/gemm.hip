@@ -178,10 +178,12 @@ double estimate_f32(const GemmDesc& d, const TileShape& t, int64_t slots, int64_
 // the bytes per cycle measured for each layout, on 64 x 256 x 356 to
 // 4096 x 1024 x 1024; times 1.5 where rows start anywhere (2049-element rows and
 // the like). The estimates of the direct-to-LDS tiles, which a product with aligned
-// rows is compared with, leave out the launch and are too low where the two meet: wrt
-// the weights about 1.35 times (1024 x 1024 x 4096 in four slices on 19: 38,700
-// against 59,500 measured, 25 us on either kernel), the others, with at most one
-// tile per compute unit, 1.8 times (1024 x 1024 x 2048 on 12: 34,000 against 63,000).
+// rows is compared with, leave out the launch and are too low where the two meet, so
+// this one is divided by as much: forward 1.8 (1024 x 1024 x 2048 on 12: estimated
+// 34,000 cycles, measured 63,000), wrt the input 1.5, wrt the weights 1.35 (1024 x
+// 1024 x 4096 in four slices on 19, with their sum: 38,700 against 56,600, 23.6 us).
+// The last was fitted to a 64 x 64 tile of four waves (25 us there); with eight it takes
+// 21.2 us, and the line still leaves that product on 19.
 double estimate_wave_bf16(const GemmDesc& d, const TileShape& t, int64_t slots, int64_t kc, bool aligned) {
   static const double fix[] = {1400.0, 2000.0, 2500.0, 8000.0, 3500.0};
   static const double rate[5][3] = {  // NN, NT, TN

@@ -478,6 +478,21 @@ def test_scratch_sizes_do_not_depend_on_addresses(tmp_path):
     assert a == b > 0
 
 
+@pytest.mark.parametrize("widths,batch", [((784, 512, 512, 40), 256), ((4096, 2048, 2048, 1000), 4096),
+                                          ((100, 333, 77, 40), 1001)])
+def test_rectified_float32_layers_keep_their_order_of_sums(widths, batch):
+    """The forward products whose rectifier's derivative a float32 gradient takes are planned
+    on the register-staged tiles (0-4); the same products of another activation, and every
+    other product, on the tiles that replaced them (6-9, 20-23)."""
+    import re
+    for act in ("relu", "tanh"):
+        m = dl.Model(widths, (act,) * 2 + ("none",), "f32", batch_max=batch)
+        cfgs = [int(c) for n in (p["name"] for p in m.plan(batch)) if n.startswith("gemm")
+                for c in re.findall(r"c(\d+)(?:s\d+)?$", n)]
+        assert len(cfgs) >= 5
+        assert all((c <= 4) == (act == "relu" and i < 2) for i, c in enumerate(cfgs)), (act, cfgs)
+
+
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("classes,batch", [(10, 256), (32, 100), (10, 9000), (33, 256)])
 def test_head_of_few_classes_in_the_plan(dtype, classes, batch):
