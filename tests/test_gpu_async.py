@@ -25,7 +25,7 @@ import pytest
 import oracle
 import paper_1711_03016_amd as dl
 import workloads
-from helpers import TOL, assert_close, device, quant, rel_l2, to_dev, to_np
+from helpers import TOL, assert_close, assert_forced, device, quant, rel_l2, to_dev, to_np
 
 pytestmark = pytest.mark.gpu
 
@@ -52,6 +52,7 @@ def cfg(request, monkeypatch):
 def test_async_forward(cfg, shape):
     import torch
     M, N, K = shape
+    assert_forced(cfg, M, N, K, "bf16", lambda layout, n: layout != "tn" or cfg not in (16, 18))
     r = _rng(11, M, N, K)
     X = r.standard_normal((M, K)).astype(np.float32)
     W = (r.standard_normal((K, N)) / np.sqrt(K)).astype(np.float32)
@@ -100,6 +101,8 @@ def test_async_backward_params(cfg, shape):
     """dW[K,N] = X[M,K]^T.dY[M,N] and db = column sums of dY; the contraction runs over M."""
     import torch
     M, N, K = shape
+    if cfg in (16, 18):
+        pytest.skip("64-row tiles do not run products wrt the weights")
     r = _rng(13, M, N, K)
     X = r.standard_normal((M, K)).astype(np.float32)
     dY = (r.standard_normal((M, N)) * 0.01).astype(np.float32)

@@ -12,7 +12,7 @@ import numpy as np
 import pytest
 
 import paper_1711_03016_amd as dl
-from helpers import device, quant, to_np
+from helpers import assert_forced, device, planned_config, quant, to_np
 
 pytestmark = pytest.mark.gpu
 
@@ -55,6 +55,7 @@ def _near(got, ref, magnitude, K, out_dtype, what):
 def test_layer(cfg, shape, out_dtype):
     import torch
     M, N, K = shape
+    assert_forced(cfg, M, N, K, "bf16", lambda layout, n: cfg != 2 or n <= 32)  # (2: narrow outputs)
     r = np.random.default_rng([41, M, N, K])
     X = r.standard_normal((M, K)).astype(np.float32)
     W = (r.standard_normal((K, N)) / np.sqrt(K)).astype(np.float32)
@@ -82,6 +83,7 @@ def test_layer(cfg, shape, out_dtype):
 @pytest.mark.parametrize("M,Kx,Kh", [(33, 7, 20), (65, 100, 256), (130, 33, 61), (17, 1, 1), (50, 72, 9)])
 def test_two_phase_cell(cfg, M, Kx, Kh):
     import torch
+    assert (planned_config("nn", "bf16", M, Kh, Kx + Kh, Kx) == cfg) == (cfg != 2 or Kh <= 32)
     r = np.random.default_rng([42, M, Kx, Kh])
     X = r.standard_normal((M, Kx)).astype(np.float32)
     H = r.standard_normal((M, Kh)).astype(np.float32)

@@ -8,12 +8,14 @@ most about K 2^-24 times the sum of the terms' magnitudes (element by element;
 8 more roundings are allowed for the epilogue). A single wrong or missing term is
 about 1/K of that sum, far outside for these K.
 """
+import re
+
 import numpy as np
 import pytest
 
 import oracle
 import paper_1711_03016_amd as dl
-from helpers import assert_close, device, to_dev, to_np
+from helpers import assert_close, assert_forced, device, planned_config, to_dev, to_np
 
 pytestmark = pytest.mark.gpu
 
@@ -64,6 +66,7 @@ def _layer(M, N, K):
 
 @pytest.mark.parametrize("shape", SHAPES)
 def test_layer(cfg, shape):
+    assert_forced(cfg, *shape, "f32")
     _layer(*shape)
 
 
@@ -119,6 +122,7 @@ def test_far_leading_dimensions(shape):
 def test_two_phase_cell(cfg, M, Kx, Kh):
     """Both phases end inside a step; each reads its own operand up to its own end."""
     import torch
+    assert planned_config("nn", "f32", M, Kh, Kx + Kh, Kx) == cfg
     r = np.random.default_rng([32, M, Kx, Kh])
     X = r.standard_normal((M, Kx)).astype(np.float32)
     H = r.standard_normal((M, Kh)).astype(np.float32)
@@ -165,7 +169,9 @@ def test_paired_adjoints(cfg, widths, batch, monkeypatch):
     wl = replace(workloads.WORKLOADS["c2"], widths=widths, acts=("tanh", "sigmoid", "none"), batch=batch)
     x, params, y = workloads.make_inputs(wl, bias_scale=0.1)
     m = dl.Model(widths, wl.acts, "f32", "softmax_ce", True, batch)
-    assert any(p["name"].startswith("gemm_pair") for p in m.plan(batch))
+    names = [p["name"] for p in m.plan(batch)]
+    assert any(n.startswith("gemm_pair") for n in names)
+    assert all(re.search(rf"c{cfg}(s\d+)?$", n) for n in names if n.startswith("gemm") and "xent" not in n), names
     P = m.pack(params, device(), torch.float32)
     ws = torch.empty(m.workspace_bytes(batch), dtype=torch.uint8, device=device())
     outs = []

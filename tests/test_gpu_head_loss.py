@@ -87,6 +87,7 @@ def test_chain_in_epilogue_on_every_tile(cfg, n, batch, monkeypatch):
     outs = []
     for epi in (True, False):
         m = dl.Model((n, n), ("none",), "f32", "chain8", True, batch, chain_in_epilogue=epi)
+        assert m.plan(batch)[0]["name"].endswith(f"c{cfg}")
         P = m.pack([(W, b)], device(), torch.float32)
         ws = torch.full((m.workspace_bytes(batch),), 0xFF, dtype=torch.uint8, device=device())
         loss, dx = torch.empty(1, device=device()), torch.empty((batch, n), device=device())

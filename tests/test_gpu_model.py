@@ -7,6 +7,8 @@ of a few base rows repeated in a seeded order: the mean loss and its gradient
 over such a batch equal those over the base rows, and every row's forward value
 and input gradient equal those of its base row.
 """
+import re
+
 import numpy as np
 import pytest
 
@@ -559,15 +561,13 @@ def _chain_run(wl, x, params, chain_in_epilogue, B):
     return loss.item(), dP.cpu(), dx.cpu(), m
 
 
-@pytest.mark.parametrize("widths,batch,cfg", [((4096, 4096), 256, None), ((200, 200), 300, None),
-                                              ((200, 200), 300, 0), ((200, 200), 300, 1),
-                                              ((200, 200), 300, 2), ((200, 200), 300, 3),
-                                              ((200, 200), 300, 4), ((200, 200), 300, 5)])
+@pytest.mark.parametrize("widths,batch,cfg", [((4096, 4096), 256, None), ((200, 200), 300, None)] +
+                         [((200, 200), 300, c) for c in (6, 7, 8, 9, 20, 21, 22, 23)])
 def test_chain_in_epilogue(widths, batch, cfg, monkeypatch):
     """The eight-operator chain run in the dense product's epilogue (z never
     stored) against the oracle and, bit for bit in dparams and dx, against the
     standalone chain kernel (same element arithmetic; only the loss partials
-    are grouped differently). Every register-staged configuration forced."""
+    are grouped differently). Every configuration that has the epilogue forced."""
     from dataclasses import replace
     if cfg is not None:
         monkeypatch.setenv("DLVM_GEMM_CONFIG", str(cfg))
@@ -584,7 +584,7 @@ def test_chain_in_epilogue(widths, batch, cfg, monkeypatch):
     assert rel_l2(to_np(gb), rg[0][1]) <= TOL["f32"]
     assert rel_l2(to_np(d1), rdx) <= TOL["f32"]
     names = [p["name"] for p in m.plan(batch)]
-    assert any(n.startswith("gemm_nn_chain8") for n in names)
+    assert any(n.startswith("gemm_nn_chain8") and (cfg is None or n.endswith(f"c{cfg}")) for n in names)
     assert "chain8" not in names
 
 
@@ -603,6 +603,7 @@ def torch_equal(a, b):
     ((6, 3), ("none",), 600, True),                              # a large batch (LDS nearly full)
     ((8, 8, 4), ("relu", "none"), 400, False),
     ((12,) * 8 + (10,), ("tanh",) * 7 + ("none",), 8, True),     # the most layers it takes
+    ((1,) * 8 + (2,), ("tanh",) * 7 + ("none",), 840, True),     # rows end to end: padded they do not fit
 ])
 def test_small_network_path(widths, acts, batch, wrt_x, monkeypatch):
     """The one-workgroup gradient of a small float32 network against the
@@ -635,22 +636,34 @@ def test_small_network_path(widths, acts, batch, wrt_x, monkeypatch):
 
 
 
-@pytest.mark.parametrize("dtype", ["f32", "bf16"])
-@pytest.mark.parametrize("cfg", [0, 1, 2, 3, 4, 5])
+@pytest.mark.parametrize("dtype,cfg", [("f32", c) for c in (0, 1, 3, 4, 5)] +
+                         [("bf16", c) for c in range(6)])
 @pytest.mark.parametrize("batch", [300, 7])
 def test_forced_tile_configurations(dtype, cfg, batch, monkeypatch):
-    """Every register-staged tile configuration forced on a ragged network:
-    forward (NN), adjoint wrt the input (NT) and wrt the weights (TN, paired
-    with NT where the configuration allows), against the oracle. The
+    """Every register-staged tile configuration forced on a ragged network,
+    against the oracle: in bf16 the forward (NN), the adjoint wrt the input (NT)
+    and wrt the weights (TN, paired with NT where the configuration allows), in
+    float32 the rectified layer's forward, which alone runs on these tiles. The
     contraction lengths 520, 300, 150, 72 and 10 give odd, even and single
     stage counts (128 k per stage in float32, 256 in bf16 for the 4-segment
     tiles) and K not a multiple of the vector width (150, 10, and a batch of 7
-    for the products wrt the weights), where the loads go element by element."""
+    for the products wrt the weights), where a row's last load starts early or
+    goes element by element."""
     from dataclasses import replace
     monkeypatch.setenv("DLVM_GEMM_CONFIG", str(cfg))
     base = workloads.WORKLOADS["c2" if dtype == "f32" else "c3"]
     wl = replace(base, widths=(520, 150, 72, 10), acts=("tanh", "relu", "none"), batch=batch,
                  wrt_x=True)
+    m = dl.Model(wl.widths, wl.acts, wl.dtype, wl.loss, True, batch)
+    names = [re.sub(r"s\d+$", "", p["name"]) for p in m.plan(batch) if p["name"].startswith("gemm")]
+    names = [n for n in names if "xent" not in n]  # (ten classes: the head runs on its own tile)
+    forced = [n.split("_")[1] for n in names if n.endswith(f"c{cfg}")]
+    if dtype == "f32":                                     # 520-150 is tanh, 150-72 rectified
+        assert forced == ["nn"] and names[1].endswith(f"c{cfg}"), names
+    elif cfg == 2:                                         # outputs of at most 32 columns
+        assert forced == ["tn"], names
+    else:
+        assert forced == [n.split("_")[1] for n in names], names
     x, params, y = workloads.make_inputs(wl, bias_scale=0.1)
     got = _run(wl, x, params, y, wrt_x=True)
     rl, rg, rdx = oracle.mlp_gradient(_spec(wl), x, params, y, wrt_x=True)

@@ -16,7 +16,7 @@ import pytest
 import oracle
 import paper_1711_03016_amd as dl
 import workloads
-from helpers import TOL, device, rel_l2, to_dev, to_np, torch_dtype
+from helpers import TOL, device, planned_config, rel_l2, to_dev, to_np, torch_dtype
 
 pytestmark = pytest.mark.gpu
 
@@ -51,13 +51,16 @@ def test_cell_forward(dtype, act, M, Kx, H):
     assert out.device == dev
 
 
-@pytest.mark.parametrize("dtype,cfg", [("f32", c) for c in (0, 1, 3, 4, 5)] +
+@pytest.mark.parametrize("dtype,cfg", [("f32", c) for c in (6, 7, 8, 9, 20, 21, 22, 23)] +
                          [("bf16", c) for c in (0, 1, 3, 4, 10, 11, 12, 13, 14, 16, 17, 18, 19)])
 def test_cell_forward_every_configuration(dtype, cfg, monkeypatch):
     """Each tile configuration forced on a two-phase product whose phases both
     end inside a k-tile and whose rows and columns are ragged (a configuration
     that cannot run a two-phase product, 14, falls back)."""
     M, Kx, H = 300, 40, 72
+    with monkeypatch.context() as forced:
+        forced.setenv("DLVM_GEMM_CONFIG", str(cfg))
+        assert (planned_config("nn", dtype, M, H, Kx + H, Kx) == cfg) == (cfg != 14)
     wl, (xs, h0, W, U, b, _) = _case(1, Kx, H, M, dtype, "tanh", seed=5)
     monkeypatch.setenv("DLVM_GEMM_CONFIG", str(cfg))
     out = torch_zeros((M, H), dtype)
