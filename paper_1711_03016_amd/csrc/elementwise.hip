@@ -382,7 +382,7 @@ __global__ __launch_bounds__(kBlock) void dlvm_chain8_kernel(
 //
 // One workgroup, so its time is round trips: 16 waves with four loads of each
 // array in flight per thread (4,096 partials at once; one load at a time by 256
-// threads took 16 round trips, 6.1 us for the 4,096 partials of a 16384-row loss
+// threads took 16 round trips, 6.2 us for the 4,096 partials of a 16384-row loss
 // against 3.8 now), and the gaps shared out over the waves (one after the other, each
 // with its kernel-argument reads, 4.6 us for six gaps).
 // ---------------------------------------------------------------------------

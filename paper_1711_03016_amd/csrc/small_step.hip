@@ -9,8 +9,8 @@
 //             loads where whole), all loads issued before the first store so
 //             that HBM latency is paid once;
 //   forward   H_{l+1} = act_l(H_l . W_l + b_l), the last layer giving logits;
-//   loss      softmax cross-entropy, one wave per row, and the adjoint of the
-//             logits (p - onehot) / B;
+//   loss      softmax cross-entropy (16 lanes per row up to 16 classes, else one
+//             wave per row), and the adjoint of the logits (p - onehot) / B;
 //   adjoint   per layer from the last: dW_l = H_l^T dZ, db_l = colsum dZ,
 //             dZ_{l-1} = (dZ . W_l^T) * act'(H_l) (dx = dZ . W_0^T when x is
 //             differentiated; the first layer's input adjoint is otherwise dead);
@@ -67,7 +67,9 @@ __device__ __forceinline__ int wave_or(int v) {
 // holds row 4 g + r, column l. Four accumulators take the instructions in turn: independent of each other,
 // and shorter sums (outputs against float64 over 24 small networks: 1.11e-7 of the norm
 // with two accumulators, 1.02e-7 with four, 1.06e-7 with lanes sharing a sum; 64-32-10
-// at batch 16 takes 7.7 us with two and 7.6 with four).
+// at batch 16 takes 7.7 us with two and 7.6 with four; over 250 networks of 8-128 inputs,
+// batch 1-64, the four's errors are 0.93-0.98 of those of the shared sums in every
+// gradient, though single networks go either way).
 __device__ __forceinline__ f32x4 lds_tile(const float* __restrict__ a, int am, int ak, int M,
                                           const float* __restrict__ b, int bn, int bk, int N, int K,
                                           int lane) {
