@@ -64,12 +64,12 @@ __device__ __forceinline__ int wave_or(int v) {
 // for the tile's rows m < M (rows past it are read from row 0 and give outputs that
 // are not stored), B(k, n) at b[n * bn + k * bk] for n < N. Lane 16 g + l of an
 // instruction holds row (column) l at the g-th of its 4 k; the result's register r
-// holds row 4 g + r, column l. Four accumulators take the instructions in turn: independent of each other,
-// and shorter sums (outputs against float64 over 24 small networks: 1.11e-7 of the norm
-// with two accumulators, 1.02e-7 with four, 1.06e-7 with lanes sharing a sum; 64-32-10
-// at batch 16 takes 7.7 us with two and 7.6 with four; over 250 networks of 8-128 inputs,
-// batch 1-64, the four's errors are 0.93-0.98 of those of the shared sums in every
-// gradient, though single networks go either way).
+// holds row 4 g + r, column l. Four accumulators take the instructions in turn:
+// independent of each other, and shorter sums (outputs against float64 over 24 small
+// networks: 1.11e-7 of the norm with two accumulators, 1.02e-7 with four, 1.06e-7 with
+// lanes sharing a sum; 64-32-10 at batch 16 takes 7.7 us with two and 7.6 with four; over
+// 250 networks of 8-128 inputs, batch 1-64, the four's errors are 0.93-0.98 of those of
+// the shared sums in every gradient, though single networks go either way).
 __device__ __forceinline__ f32x4 lds_tile(const float* __restrict__ a, int am, int ak, int M,
                                           const float* __restrict__ b, int bn, int bk, int N, int K,
                                           int lane) {
